@@ -1,30 +1,35 @@
 // Persistent frame kernel for gfx950.
 //
-// One workgroup (16 waves) owns a strip of rows (which may cross one tile
-// edge) for a range of frames.  The strip's dark and 1/gain planes are loaded once into registers
-// and stay there for every frame; only the 2-byte raw words stream from HBM.
-// Per frame:
-//   phase 1a (each wave, its own bank-rows): load raw words (prefetched one
-//     frame ahead), correct them (Fig. b) and write u to LDS;
-//   phase 1b (all waves): every bank-row's lower median, exactly, by a
-//     bracketing count search with L lanes per bank-row (common mode, Fig. c);
-//     the same lanes then test their values against the seed threshold the
-//     median implies and append the seed pixels to a workgroup list;
-//   phase 1c (each wave, its own bank-rows): Frames2 if kept, one frame later;
-//   phase 2 (all waves, over the pooled seeds): 3x3 local maximum with the
-//     raster tie-break, masked 3x3 charge sum, photon count (Fig. e and the
-//     charge summing section); hits mark a per-bank-row column bitmap;
-//   phase 3 (wave 0): prefix over bank-rows, staging chunk claim;
-//   phase 4 (all waves): each hit's raster position = bank-row prefix +
-//     number of hits left of it in its bank-row (bitmap popcount).
+// One workgroup (8 waves, two workgroups a compute unit) owns a strip of rows
+// (which may cross one tile edge) for a range of frames.  A group of L lanes
+// holds a bank-row (B pixels of one row) in registers, V values a lane, with
+// its dark and 1/gain, which stay there for every frame; only the 2-byte raw
+// words stream from HBM.  Per frame:
+//   phase 1 (each wave, its own bank-rows): the raw words (loaded a frame
+//     ahead) are corrected in registers (Fig. b), every bank-row's lower median
+//     is found, exactly, by a bracketing count search (common mode, Fig. c), and
+//     Frames2 goes to LDS; the same lanes test their values against the seed
+//     threshold and append the seed pixels to a workgroup list;
+//   phase 2 (over the pooled seeds): 3x3 local maximum with the raster
+//     tie-break, masked 3x3 charge sum, photon count (Fig. e and the charge
+//     summing section); hits mark a per-bank-row column bitmap;
+//   phase 3 (one wave): staging chunk claim;
+//   phase 4: each hit's raster position = bank-row prefix + number of hits
+//     left of it in its bank-row (bitmap popcount).
 //
-// Lane layouts.  Phases 1a and 1c: a bank-row (B pixels of one row) is held
-// by one wave as NQ pair-slots; lane l of pair-slot q holds columns 128q + 2l
-// and 128q + 2l + 1 of the bank (value-slots 2q and 2q+1); absent pixels hold
-// +inf.  Phase 1b: bank-row i belongs to lane group i % (64 / L) of wave
-// i / (64 / L) (single-gain kernels with a row step: a wave's four groups
-// take every fourth row, see the median groups' lane constants); lane j of
-// the group holds columns L v + j, v < V.
+// What bounds it: VALU instructions.  On the 10,000-frame CSPAD batch at
+// occupancy 0.01 it issues about 5,900 wave instructions per strip-frame of 30
+// own rows (the form before this one 8,000: 16 waves of four 16-lane groups,
+// values through LDS) and the VALUs are busy about 80 % of the time (66 %);
+// the batch takes 27.9 ms with default strips and frame groups, 42.6 ms before.
+// What the two changes behind that give:
+//   - few lanes a bank-row: a wave searches 8 (194-pixel banks) or 16 (96)
+//     medians at once, so the search's reductions, control and sort, as many
+//     instructions as the work on the values, are paid for twice the bank-rows;
+//   - a bank-row's values never leave its lanes' registers between the raw
+//     words and the seeds, so one wave's medians wait for no other wave's
+//     corrections, and the two workgroups of a compute unit fill each other's
+//     waits at the barriers.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -39,19 +44,16 @@ namespace pdc {
 #ifdef PDC_PHASE_TIMERS
 // Tracing build only (PDC_PHASE_TIMERS): shader-clock cycles each wave spends
 // in each phase of the persistent kernel's frame loop, summed over the launch:
-// [wave][0 A, 1 A->B barrier, 2 medians, 3 seeds, 4 local maxima, 5 hit
-// writes, 6 B->A barrier, 7 unused].
+// [wave][0 A, 1 wait at barrier 1, 2 medians, 3 seeds, 4 wait at barrier 2,
+// 5 local maxima, 6 hit writes, 7 unused].
 __device__ unsigned long long g_phase_cycles[kV2Waves * 8];
 #endif
 
 
-__device__ __forceinline__ uint32_t popc64(uint64_t m) { return (uint32_t)__popcll(m); }
-
-__device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
-
-__device__ __forceinline__ float uniform_f(float x)
+// Number of set bits of m below this lane.
+__device__ __forceinline__ int mbcnt(uint64_t m)
 {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
 // Workgroup barrier for LDS only: it waits for the wave's own LDS accesses,
@@ -63,6 +65,16 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Orders this wave's LDS accesses before the ones that follow, without
+// waiting for its global loads (a wave's LDS instructions complete in order;
+// the compiler must not move them across).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
 // Inclusive prefix sum over the 64 lanes (DPP row shifts, then row
@@ -127,28 +139,29 @@ __device__ __forceinline__ bool done_single(float lo, float hi)
 }
 
 // Rough location of an L-lane group's median: medians of three of each lane's
-// values (up to eight triples), averaged over the group.  Dense banks (no +inf
+// values (up to eight triples, of columns far apart: a photon's cloud covers
+// neighbours), averaged over the group.  Dense banks (no +inf
 // inside the first B columns) take the triples that every lane holds; with
 // invalid pixels (SPARSE) each lane takes the finite ones.  Only the work of
 // the searches below depends on it, never their result.
 template <int V, int L, bool SPARSE>
-__device__ __forceinline__ float group_estimate(const float (&x)[V], int B)
+__device__ __forceinline__ float group_estimate(const float (&x)[V], bool full)
 {
     static_assert(V >= 3, "the start estimate takes triples of values per lane");
     constexpr int NT = V / 3 < 8 ? V / 3 : 8;
-    if (!SPARSE && B >= 3 * L * NT) {  // uniform: every lane's NT triples lie inside the bank
-        float s3 = __builtin_amdgcn_fmed3f(x[0], x[1], x[2]);
+    if (!SPARSE && full) {  // uniform: every lane's NT triples lie inside the bank
+        float s3 = __builtin_amdgcn_fmed3f(x[0], x[NT], x[2 * NT]);
 #pragma unroll
-        for (int t = 1; t < NT; ++t) s3 += __builtin_amdgcn_fmed3f(x[3 * t], x[3 * t + 1], x[3 * t + 2]);
+        for (int t = 1; t < NT; ++t) s3 += __builtin_amdgcn_fmed3f(x[t], x[t + NT], x[t + 2 * NT]);
         return gsum_f<L>(s3) * (1.0f / (float)(NT * L));
     }
     float s3 = 0.0f;
     int n3 = 0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        const float a = x[3 * t];
-        const float b = x[3 * t + 1] < INFINITY ? x[3 * t + 1] : a;
-        const float c = x[3 * t + 2] < INFINITY ? x[3 * t + 2] : b;
+        const float a = x[t];
+        const float b = x[t + NT] < INFINITY ? x[t + NT] : a;
+        const float c = x[t + 2 * NT] < INFINITY ? x[t + 2 * NT] : b;
         if (a < INFINITY) {
             s3 += __builtin_amdgcn_fmed3f(a, b, c);
             ++n3;
@@ -163,93 +176,174 @@ __device__ __forceinline__ float group_estimate(const float (&x)[V], int B)
 // bit j of its place in the group is clear (it keeps the smaller value of a
 // pair) and +inf otherwise.  Made once per kernel and kept in registers (an
 // opaque copy, so that the compiler does not recompute them per use).
+template <int L>
 struct SortSides {
-    float e[4];
+    static constexpr int N = L == 4 ? 2 : (L == 8 ? 3 : 4);
+    float e[N];
 };
 
 template <int L>
-__device__ __forceinline__ SortSides sort_sides()
+__device__ __forceinline__ SortSides<L> sort_sides()
 {
     const int gl = __lane_id() & (L - 1);
-    SortSides sd;
+    SortSides<L> sd;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < SortSides<L>::N; ++j) {
         sd.e[j] = (gl >> j) & 1 ? INFINITY : -INFINITY;
         asm volatile("" : "+v"(sd.e[j]));
     }
     return sd;
 }
 
-// Ascending bitonic sort of one value per lane over an aligned L-lane group,
-// then the value of lane r broadcast to the group.  Merges of size 2b start
-// with the mirror partner inside the block, then halve with xor partners; a
-// compare-exchange is one median of three: med3(y, partner, -inf) is the
-// smaller of the two (kept by the lower lane of the pair), med3(y, partner,
-// +inf) the larger (no NaN is present).  The pick is an OR over the group of
-// the chosen lane's bits and zeros elsewhere.  All lanes must be active.
-template <int L>
-__device__ __forceinline__ float group_sort_pick(float y, int r, const SortSides &sd)
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float x)
 {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror4 = 0x1B, kMirror8 = 0x141, kMirror16 = 0x140;
+
+// Compare-exchange of every register with the same (REV: the mirrored)
+// register of the partner lane: a median of three with the lane's side keeps
+// the smaller or the larger value (no NaN is present).
+template <int S, int CTRL, bool REV>
+__device__ __forceinline__ void cx_lanes(float (&y)[S], float e)
+{
+    float p[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) p[s] = dpp_f<CTRL>(y[REV ? S - 1 - s : s]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) y[s] = __builtin_amdgcn_fmed3f(y[s], p[s], e);
+}
+// Compare-exchange of registers a < b of one lane.
+__device__ __forceinline__ void cx_regs(float &a, float &b)
+{
+    float lo, hi;
+    asm("v_min_f32 %0, %1, %2" : "=v"(lo) : "v"(a), "v"(b));
+    asm("v_max_f32 %0, %1, %2" : "=v"(hi) : "v"(a), "v"(b));
+    a = lo;
+    b = hi;
+}
+// The rest of a merge inside a lane: half-cleaners of distances S/2 .. 1, for
+// S = 3 (the half-cleaners across lanes split any even length) a sort.
+template <int S>
+__device__ __forceinline__ void cx_inner(float (&y)[S])
+{
+    if constexpr (S == 4) {
+        cx_regs(y[0], y[2]);
+        cx_regs(y[1], y[3]);
+        cx_regs(y[0], y[1]);
+        cx_regs(y[2], y[3]);
+    } else if constexpr (S == 3) {
+        cx_regs(y[0], y[1]);
+        cx_regs(y[1], y[2]);
+        cx_regs(y[0], y[1]);
+    } else {
+        cx_regs(y[0], y[1]);
+    }
+}
+
+// Ascending bitonic sort of the S L values of an aligned L-lane group (value
+// j in register j % S of lane j / S), then value r (group-uniform) broadcast
+// to the group.  Merges start with the mirror partner inside the block, then
+// halve with xor partners.  The pick is an OR over the group of the chosen
+// lane's bits and zeros elsewhere.  All lanes must be active.
+template <int L, int S>
+__device__ __forceinline__ float group_sort_pick(float (&y)[S], int r, const SortSides<L> &sd)
+{
+    static_assert((S == 2 || S == 3 || S == 4) && (L == 4 || L == 8 || L == 16), "compiled layouts");
     const int gl = __lane_id() & (L - 1);
-    const float e1 = sd.e[0], e2 = sd.e[1], e4 = sd.e[2], e8 = sd.e[3];
-#define PDC_CX(partner, e) y = __builtin_amdgcn_fmed3f(y, (partner), (e));
-#define PDC_DPP(ctrl) __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(y), ctrl, 0xF, 0xF, false))
-    PDC_CX(PDC_DPP(0xB1), e1)                      // merge 2: mirror (xor 1)
-    if (L >= 4) {
-        PDC_CX(PDC_DPP(0x1B), e2)                  // merge 4: mirror in 4
-        PDC_CX(PDC_DPP(0xB1), e1)
+    if constexpr (S == 4) {
+        cx_regs(y[0], y[1]);
+        cx_regs(y[2], y[3]);
+        cx_regs(y[0], y[3]);
+        cx_regs(y[1], y[2]);
+        cx_regs(y[0], y[1]);
+        cx_regs(y[2], y[3]);
+    } else {
+        cx_inner(y);
     }
-    if (L >= 8) {
-        PDC_CX(PDC_DPP(0x141), e4)                 // merge 8: row_half_mirror
-        PDC_CX(PDC_DPP(0x4E), e2)                  // xor 2
-        PDC_CX(PDC_DPP(0xB1), e1)
+    cx_lanes<S, kXor1, true>(y, sd.e[0]);  // merge across 2 lanes
+    cx_inner(y);
+    cx_lanes<S, kMirror4, true>(y, sd.e[1]);  // across 4
+    cx_lanes<S, kXor1, false>(y, sd.e[0]);
+    cx_inner(y);
+    if constexpr (L >= 8) {
+        cx_lanes<S, kMirror8, true>(y, sd.e[2]);
+        cx_lanes<S, kXor2, false>(y, sd.e[1]);
+        cx_lanes<S, kXor1, false>(y, sd.e[0]);
+        cx_inner(y);
     }
-    if (L >= 16) {
-        PDC_CX(PDC_DPP(0x140), e8)                 // merge 16: row_mirror
-        {
-            // xor 4 = xor 3 (quad mirror) then xor 7 (half-row mirror)
-            const int t = __builtin_amdgcn_mov_dpp(__float_as_int(y), 0x1B, 0xF, 0xF, false);
-            PDC_CX(__int_as_float(__builtin_amdgcn_mov_dpp(t, 0x141, 0xF, 0xF, false)), e4)
-        }
-        PDC_CX(PDC_DPP(0x4E), e2)
-        PDC_CX(PDC_DPP(0xB1), e1)
+    if constexpr (L >= 16) {
+        cx_lanes<S, kMirror16, true>(y, sd.e[3]);
+        // xor 4 = xor 3 (quad mirror) then xor 7 (half-row mirror)
+        float p[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) p[s] = dpp_f<kMirror8>(dpp_f<kMirror4>(y[s]));
+#pragma unroll
+        for (int s = 0; s < S; ++s) y[s] = __builtin_amdgcn_fmed3f(y[s], p[s], sd.e[2]);
+        cx_lanes<S, kXor2, false>(y, sd.e[1]);
+        cx_lanes<S, kXor1, false>(y, sd.e[0]);
+        cx_inner(y);
     }
-#undef PDC_DPP
-#undef PDC_CX
-    int rb = gl == r ? __float_as_int(y) : 0;
+    // value r is register r - S (r / S) of lane r / S (r < S L <= 32, or group-
+    // uniform rubbish that no lane picks)
+    const int rl = S == 3 ? (r * 43) >> 7 : r / S;
+    float z = y[0];
+#pragma unroll
+    for (int s = 1; s < S; ++s) z = r - S * rl == s ? y[s] : z;
+    int rb = gl == rl ? __float_as_int(z) : 0;
 #define PDC_GX(ctrl) rb |= __builtin_amdgcn_update_dpp(0, rb, ctrl, 0xF, 0xF, false);
-    PDC_GX(0xB1)
-    if (L >= 4) PDC_GX(0x4E)
-    if (L >= 8) PDC_GX(0x141)
-    if (L >= 16) PDC_GX(0x140)
+    PDC_GX(kXor1)
+    PDC_GX(kXor2)
+    if (L >= 8) PDC_GX(kMirror8)
+    if (L >= 16) PDC_GX(kMirror16)
 #undef PDC_GX
     return __int_as_float(rb);
 }
 
-// Exact element of rank k (0-based, ascending) among the nval finite values
-// held by an L-lane group (V values per lane, absent values +inf, lane value
-// v also at src[L v] in LDS); every group of the wave searches its own bank
-// at once.  Bracketing search on counts, count(x < lo) <= k < count(x < hi)
-// throughout, with the lane masks of both bounds kept: the first bracket is
-// the estimate and a bound placed from its count (widening until they
-// bracket), later steps
-// interpolate the pivot from the bracket counts and bisect in key space when
-// the interpolated pivot is not strictly inside or the bracket stopped
-// halving.  Once at most L values remain in [lo, hi) (the lane's are the bits
-// of mhi & ~mlo) they are gathered from LDS into the group's lanes, sorted
-// across them, and the answer is read off; a bracket that holds a single float
-// (possibly many copies of it) gives that float.  Groups with act false return
-// an unspecified value.
-template <int V, int L, bool SPARSE>
-__device__ float group_median(const float (&x)[V], const float *src, int nval, int k, float rw, bool act,
-                              float *gsc, int B, const SortSides &sd)
+// Slot v of a lane: offset from the lane's first column of its bank-row (the
+// first 8 Q slots are chunks of 8 columns, 8 L apart; the R after them single
+// columns, L apart, from column 8 L Q + gl).
+template <int L, int Q, int R>
+__device__ __forceinline__ int slot_off(int v, int gl)
 {
-    const float est = group_estimate<V, L, SPARSE>(x, B);
+    const int o = v + (v & ~7) * (L - 1);
+    if (R == 0) return o;
+    return v < 8 * Q ? o : 8 * L * Q - 7 * gl + L * (v - 8 * Q);
+}
+
+// Exact element of rank k (0-based, ascending) among the nval finite values
+// held by an L-lane group (V = 4 Q + R values per lane, absent values +inf,
+// slot v also at src[slot_off(v)] in LDS); every group of the wave searches
+// its own bank at once.  Bracketing search on counts, count(x < lo) <= k <
+// count(x < hi) throughout, with the lane masks of both bounds kept: the first
+// bracket is the estimate and a bound placed from its count (widening until
+// they bracket), later steps interpolate the pivot from the bracket counts and
+// bisect in key space when the interpolated pivot is not strictly inside or
+// the bracket stopped halving.  Once at most S L values remain in [lo, hi)
+// (the lane's are the bits of mhi & ~mlo) they are gathered from LDS into the
+// group's lanes, S a lane, sorted across them, and the answer is read off; a
+// bracket that holds a single float (possibly many copies of it) gives that
+// float.  Groups with act false return an unspecified value.  gsc: the
+// group's S L floats of LDS scratch.
+//
+// S and the margin of the second bound.  The work of a step is paid by the
+// whole wave while any of its 64 / L groups needs it, so the bracket that is
+// left to the sort is wide enough that few groups miss it or overfill it.  A
+// model of this search on CSPAD-like banks (194 values, 8 lanes a bank) takes
+// an extra count in 66 % of the waves with 16 values left to the sort, and in
+// 19 % with 32 and a margin of 8 to 9 ranks; with 96-pixel banks on 4 lanes
+// 60 % with 16 (32 would cost 8 registers a lane in the sort).
+template <int L, int Q, int R, int S, bool SPARSE>
+__device__ __forceinline__ float group_median(const float (&x)[8 * Q + R], const float *src, int nval, int k, float rw,
+                                              bool act, float *gsc, bool full, const SortSides<L> &sd)
+{
+    constexpr int V = 8 * Q + R, CAP = S * L, MARGIN = CAP >= 32 ? 7 : (CAP >= 24 ? 6 : 4);
+    const float est = group_estimate<V, L, SPARSE>(x, full);
 
     // First bracket in two counts: the count below the estimate gives its
-    // rank error e, and the second bound goes e + 4 rank widths beyond it on
-    // the side of rank k (the estimate misses by about 5 ranks on these
-    // banks; two bounds placed around it at once missed twice as often)
+    // rank error e, and the second bound goes e + MARGIN rank widths beyond it
+    // on the side of rank k
     float lo, hi;
     uint32_t mlo, mhi;
     int clo, chi;
@@ -257,7 +351,7 @@ __device__ float group_median(const float (&x)[V], const float *src, int nval, i
         const uint32_t m1 = lane_mask<V>(x, est);
         const int c1 = gsum_i<L>(__popc(m1));
         const bool up = c1 <= k;  // rank k lies at or above the estimate
-        const float d = (float)((up ? k + 1 - c1 : c1 - k) + 4) * rw;
+        const float d = (float)((up ? k + 1 - c1 : c1 - k) + MARGIN) * rw;
         const float p2 = up ? est + d : est - d;
         const uint32_t m2 = lane_mask<V>(x, p2);
         const int c2 = gsum_i<L>(__popc(m2));
@@ -301,8 +395,9 @@ __device__ float group_median(const float (&x)[V], const float *src, int nval, i
     }
 
     int last_n = 4 * nval;
-    bool done = !act;
+    bool done = !act || chi - clo <= CAP;
     for (int it = 0; it < 200; ++it) {
+        if (__ballot(!done) == 0) break;
         const int n = chi - clo;
         float q = lo + (hi - lo) * (((float)(k - clo) + 0.5f) * __builtin_amdgcn_rcpf((float)n));
         // q is NaN or not strictly inside when a bound is infinite
@@ -316,8 +411,7 @@ __device__ float group_median(const float (&x)[V], const float *src, int nval, i
             single = (uint32_t)(khi - klo) <= 1u;
             q = key2f((klo >> 1) + (khi >> 1) + (klo & khi & 1));
         }
-        done = done || n <= L || single;
-        if (__ballot(!done) == 0) break;
+        done = done || single;
         last_n = interp ? n : 4 * nval;
         const uint32_t mq = lane_mask<V>(x, q);
         const int cq = gsum_i<L>(__popc(mq));
@@ -331,14 +425,16 @@ __device__ float group_median(const float (&x)[V], const float *src, int nval, i
                 chi = cq;
                 mhi = mq;
             }
+            done = chi - clo <= CAP;
         }
     }
-    // Finish: the n <= L values in [lo, hi) are gathered from LDS into the
-    // group's lanes (gsc: L floats per group, in lane order), sorted across the
-    // lanes, and lane k - clo holds the answer.  A bracket that holds a single
-    // float (n > L possible) has the answer lo.
+    // Finish: the n <= S L values in [lo, hi) are gathered from LDS into the
+    // group's lanes (in lane order), sorted across them, and value k - clo is
+    // the answer.  A bracket that holds a single float (n > S L possible) has
+    // the answer lo.
     const int gl = __lane_id() & (L - 1);
-    const bool gather = !done_single(lo, hi);
+    const int n = chi - clo;
+    const bool gather = n <= CAP && !done_single(lo, hi);
     uint32_t cm = gather ? mhi & ~mlo : 0u;
     const int c = __popc(cm);
     int incl = c;
@@ -350,92 +446,77 @@ __device__ float group_median(const float (&x)[V], const float *src, int nval, i
         incl += (L == 16 || gl >= sh) ? o : 0;                                                   \
     }
     PDC_SCAN(0x111, 1)
-    if (L >= 4) PDC_SCAN(0x112, 2)
+    PDC_SCAN(0x112, 2)
     if (L >= 8) PDC_SCAN(0x114, 4)
     if (L >= 16) PDC_SCAN(0x118, 8)
 #undef PDC_SCAN
-    float *gb = gsc - gl;  // the group's L slots
-    int pos = incl - c;
+    float *dst = gsc + (incl - c);
     while (cm) {
-        const int v = __builtin_ctz(cm);
+        // two at a time, both read before either is stored
+        const int v0 = __builtin_ctz(cm);
         cm &= cm - 1u;
-        if (pos < L) gb[pos] = src[L * v];
-        ++pos;
+        const bool two = cm != 0;
+        const int v1 = two ? __builtin_ctz(cm) : v0;
+        cm &= cm - 1u;
+        const float t0 = src[slot_off<L, Q, R>(v0, gl)], t1 = src[slot_off<L, Q, R>(v1, gl)];
+        dst[0] = t0;
+        if (two) dst[1] = t1;
+        dst += 2;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const int n = chi - clo;
-    float y = (gather && gl < n) ? gb[gl] : INFINITY;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    // exactly one lane of the group (k - clo < n <= L) holds the answer
-    const float pick = group_sort_pick<L>(y, k - clo, sd);
+    wave_lds_order();
+    float y[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) y[s] = gsc[S * gl + s];
+#pragma unroll
+    for (int s = 0; s < S; ++s) y[s] = (gather && S * gl + s < n) ? y[s] : INFINITY;
+    wave_lds_order();
+    // exactly one value of the group (k - clo < n <= S L) is the answer
+    const float pick = group_sort_pick<L, S>(y, k - clo, sd);
     return gather ? pick : lo;
 }
 
-// The L-lane group's values of a bank-row: lane gl takes src[L v] (src
-// points at its first column) for L v < lim = B - gl, else pad.  Every slot
-// is read into its own register first; when tail_only (wave-uniform:
-// B > L (V - 1)) only the last slot can lie past the bank and the others
-// are kept without a test.  (Reads under the two cases in separate branches
-// put the values in different registers, and the join then copies them.)
-template <int V, int L>
-__device__ __forceinline__ void read_group(float (&x)[V], const float *src, int lim, bool tail_only, float pad)
-{
-#pragma unroll
-    for (int v = 0; v < V; ++v) x[v] = src[L * v];
-    if (!tail_only) {
-#pragma unroll
-        for (int v = 0; v < V - 1; ++v) x[v] = L * v < lim ? x[v] : pad;
-    }
-    x[V - 1] = L * (V - 1) < lim ? x[V - 1] : pad;
-}
-
 struct V2Layout {
-    uint32_t u, med, bits, cnt, seed, hl, nseed, hcnt, pref, gs, total;  // float offsets
+    uint32_t v, bits, cnt, seed, hl, hl_stride, nseed, hcnt, total;  // float offsets
 };
 
-// LDS of one workgroup (floats): u, med, bits, cnt, the seed lists and the
-// hit lists (key and charge of each local maximum, half a seed list long)
-// are double-buffered by frame parity, the seed counts kept for three frames
-// (frame f mod 3); pref and the median finish scratch gs are single.
-__device__ __host__ __forceinline__ V2Layout v2_layout(int rmax, int W, int nb, int seed_cap)
+// LDS of one workgroup (floats).  v holds one frame (Frames1 while a wave
+// searches its medians, then Frames2); the hit lists
+// (charge and strip position of each local maximum), bitmaps and counts are
+// double-buffered by frame parity, the seed counts kept for four frames (frame
+// mod 4).  Seeds and hits name their pixel by its position in the strip's
+// loaded rows (16 bits).  The median finish scratch (16 KiB) lies in the
+// hit list of the frame's own parity, which is not in use then.
+__device__ __host__ __forceinline__ V2Layout v2_layout(int rmax, int W, int B, int nb, int seed_cap, int hit_cap)
 {
     V2Layout L;
-    // W + 1 floats before u: phase 2 reads a seed's neighbours at fixed
+    // W + 1 floats before v: phase 2 reads a seed's neighbours at fixed
     // offsets from the row above, column left, without clamping (what lies
     // outside the rows or the tile is read and then masked)
     uint32_t o = ((uint32_t)W + 4u) & ~3u;
-    L.u = o;
-    o += 2u * rmax * W;
-    L.med = o;
-    o += 2u * rmax * nb;
+    L.v = o;
+    o += (uint32_t)rmax * W;
     L.bits = o;
-    o += 2u * rmax * nb * 8;
+    o += 2u * rmax * nb * ((uint32_t)(B + 31) / 32u);
     L.cnt = o;
     o += 2u * rmax * nb;
-    L.seed = o;
-    o += 2u * seed_cap;
-    o = (o + 1u) & ~1u;  // 8-byte hit entries
-    L.hl = o;
-    o += 2u * 2u * (uint32_t)(seed_cap / 2);
     L.nseed = o;
-    o += 3;
+    o += 4;
     L.hcnt = o;
     o += 2;
-    L.pref = o;
-    o += (uint32_t)rmax * nb + 1;
-    L.gs = o;
-    o += 1024;
+    L.seed = o;
+    o += ((uint32_t)seed_cap + 1u) / 2u;
+    o = (o + 3u) & ~3u;
+    L.hl = o;
+    // per parity: hit_cap charges, then hit_cap 16-bit positions
+    L.hl_stride = ((uint32_t)hit_cap + ((uint32_t)hit_cap + 1u) / 2u + 3u) & ~3u;
+    o += 2u * L.hl_stride;
     L.total = o;
     return L;
 }
 
-size_t frame_kernel_v2_lds_bytes(int rmax, int W, int nb, int seed_cap)
+size_t frame_kernel_v2_lds_bytes(int rmax, int W, int B, int nb, int seed_cap, int hit_cap)
 {
-    return (size_t)v2_layout(rmax, W, nb, seed_cap).total * 4;
+    return (size_t)v2_layout(rmax, W, B, nb, seed_cap, hit_cap).total * 4;
 }
 
 // Item (frame group, strip) of block b among n: blocks are dealt to the 8 XCDs
@@ -450,28 +531,58 @@ __device__ __forceinline__ int block_item(int b, int n)
     return before + (b >> 3);
 }
 
-// Seed key: loaded row (7 bits), bank (7 bits), column (11 bits).
-__device__ __forceinline__ uint32_t seed_key(int row, int bank, int col)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// raw words are read, and u written, at 4- and 8-byte alignment (a bank may
+// start at any even column)
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+typedef f32x4 f32x4_a8 __attribute__((aligned(8)));
+
+// The two 16-bit halves of w as binary32 (one conversion each).
+__device__ __forceinline__ float cvt_lo16(uint32_t w)
 {
-    return ((uint32_t)row << 18) | ((uint32_t)bank << 11) | (uint32_t)col;
+    float r;
+    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0" : "=v"(r) : "v"(w));
+    return r;
+}
+__device__ __forceinline__ float cvt_hi16(uint32_t w)
+{
+    float r;
+    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(r) : "v"(w));
+    return r;
 }
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Values a lane holds in the finish of the medians (a group sorts S L).
+template <int L>
+constexpr int kV2Finish = L == 4 ? 4 : (L == 8 ? 3 : 2);
 
-// Pixels of a strip's loaded rows per thread in the flat correction pass:
-// CH chunks of 4 (a strip holds at most 16 waves x 4 x 64 / L bank-rows of
-// at most 256 / 128 pixels, i.e. 16384 pixels).
-constexpr int kFlatChunks = 4;
+// Bank-rows a lane group takes one after another in a frame: 256-column banks
+// need 16 lanes for four waves per SIMD (128 registers), and two passes keep
+// their strips as high as the others' (a strip loads two halo rows).
+template <int L>
+constexpr int kV2Passes = L == 16 ? 2 : 1;
+
+// The launch's arguments, read from the argument memory (scalar loads, cached).
+// fresh() makes the fields read through it come from there at that place: read
+// once ahead of the frame loop they would need more scalar registers than a
+// wave has, and the compiler keeps the overflow in vector-register lanes, a
+// VALU instruction a reload.
+typedef const __attribute__((address_space(4))) V2Args *V2ArgsK;
+__device__ __forceinline__ V2ArgsK fresh(V2ArgsK a)
+{
+    asm volatile("" : "+s"(a));
+    return a;
+}
 
 // One workgroup's work: work item `item` of the launch over A's strips and
 // frame groups (strip item % n_strips, frame group item / n_strips).
-template <int NQ, int GMAX, int L, int V, bool KEEP, bool CMM, bool MG>
-__device__ __forceinline__ void frame_body(const V2Args &A, const int item)
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG>
+__device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
 {
-    // Single-gain kernels correct the strip as one flat block of pixels
-    // (FLAT); auto-ranging kernels keep a wave per bank-row, whose lanes
-    // look up their pixels' range planes.
-    constexpr bool FLAT = !MG;
+    constexpr int V = 8 * Q + R, G = 64 / L, S = kV2Finish<L>, P = kV2Passes<L>;
+    constexpr int kCntRegs = (kV2Threads / L * P + 63) / 64;  // bank-rows of a workgroup, 64 a register
+    constexpr int kBitWords = (8 * L * Q + L * R + 31) / 32;  // of the widest bank of this layout
+    static_assert(V <= 32, "a lane's values are bits of one mask");
     extern __shared__ __align__(16) float lds[];
 #ifdef PDC_PHASE_TIMERS
     __shared__ unsigned long long s_tm[kV2Waves * 8];
@@ -480,220 +591,195 @@ __device__ __forceinline__ void frame_body(const V2Args &A, const int item)
     __shared__ unsigned long long s_photons;
     __shared__ uint64_t s_base;
     __shared__ uint64_t s_chunk[2];  // staging chunk in use: next free entry, end
-    __shared__ uint32_t s_p2ctr, s_p4ctr;
-    uint32_t *s_p2next = &s_p2ctr;  // next phase-2 seed chunk
-    uint32_t *s_p4next = &s_p4ctr;  // next phase-4 hit chunk
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int W = A.W, B = A.B, nb = A.nb, H = A.H;
-    const V2Layout Ly = v2_layout(A.rmax, W, nb, A.seed_cap);
-    const int RW = A.rmax * W, RN = A.rmax * nb, cap = A.seed_cap, hcap = A.seed_cap / 2;
-    float *s_u = lds + Ly.u;
-    float *s_med = lds + Ly.med;
+    const int W = A->W, B = A->B, nb = A->nb, H = A->H;
+    const V2Layout Ly = v2_layout(A->rmax, W, B, nb, A->seed_cap, A->hit_cap);
+    const int RN = A->rmax * nb, cap = A->seed_cap, hcap = A->hit_cap, bw = (B + 31) / 32;
+    float *s_v = lds + Ly.v;
     uint32_t *s_bits = reinterpret_cast<uint32_t *>(lds + Ly.bits);
     uint32_t *s_cnt = reinterpret_cast<uint32_t *>(lds + Ly.cnt);
-    uint32_t *s_seed = reinterpret_cast<uint32_t *>(lds + Ly.seed);
-    uint2 *s_hl = reinterpret_cast<uint2 *>(lds + Ly.hl);
+    uint16_t *s_seed = reinterpret_cast<uint16_t *>(lds + Ly.seed);
     uint32_t *s_hcnt = reinterpret_cast<uint32_t *>(lds + Ly.hcnt);
     uint32_t *s_nseed = reinterpret_cast<uint32_t *>(lds + Ly.nseed);
-    uint32_t *s_pref = reinterpret_cast<uint32_t *>(lds + Ly.pref);
-    float *s_gs = lds + Ly.gs;  // one slot per thread: median finish scratch
 
-    const int strip = item % A.n_strips;
-    const int fg = item / A.n_strips;
-    const V2Strip S = A.strips[strip];
-    const int lr0 = S.lg0;  // global rows
-    const int R = S.lg1 - lr0;
-    const int own_lo = S.g0 - lr0, own_hi = S.g1 - lr0;
-    const int bnd = S.gb == INT32_MAX ? R : S.gb - lr0;  // loaded row where a second tile starts
-    const int BR = R * nb;
-    const uint64_t npix = (uint64_t)A.T * H * W;
-    const uint64_t f_begin = (A.n_frames * (uint64_t)fg) / A.n_fgroups;
-    const uint64_t f_end = (A.n_frames * (uint64_t)(fg + 1)) / A.n_fgroups;
-    const int kmed = (B - 1) / 2;
+    const int strip = item % A->n_strips;
+    const int fg = item / A->n_strips;
+    const V2Strip St = A->strips[strip];
+    const int lr0 = St.lg0;  // global rows
+    const int nrow = St.lg1 - lr0;
+    const int own_lo = St.g0 - lr0, own_hi = St.g1 - lr0;
+    const int bnd = St.gb == INT32_MAX ? nrow : St.gb - lr0;  // loaded row where a second tile starts
+    const int BR = nrow * nb;
+    const uint64_t npix = (uint64_t)A->T * H * W;
+    // (n_frames <= 2^31)
+    const uint32_t f_begin = (uint32_t)((A->n_frames * (uint64_t)fg) / A->n_fgroups);
+    const uint32_t f_end = (uint32_t)((A->n_frames * (uint64_t)(fg + 1)) / A->n_fgroups);
     const uint32_t row_base = (uint32_t)lr0 * (uint32_t)W;  // pixel index of loaded row 0
-    constexpr int kP3Wave = 0;  // wave that runs phase 3 (the first to issue on its SIMD)
+    constexpr int kP3Wave = kV2Waves / 2;  // wave that runs phase 3 (few of phases 2 and 4's chunks fall to it)
 
-    // lane l of pair-slot q holds bank columns 128q + 2l and 128q + 2l + 1
-    bool lane_ok[NQ];
+    // Lane constants.  Bank-row i = (p kV2Waves + wave) G + lane / L belongs to
+    // the lane's group in pass p of P; lane gl of the group holds, in slots
+    // 8 c + s (c < Q), columns 8 (gl + L c) + s and, in slots 8 Q + r, columns
+    // 8 L Q + L r + gl.  A group past the last bank-row repeats bank-row 0 and
+    // stores nothing.  o4: strip position of slot 0; vmask: the slots inside
+    // the bank.
+    const SortSides<L> sides = sort_sides<L>();  // the bank-median finish's sort
+    const int gl = lane & (L - 1);
+    const bool full = B >= 8 * L * Q;  // (uniform) only the R single slots may lie past the bank
+    uint32_t vmask = 0;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) lane_ok[q] = 128 * q + 2 * lane < B;
-    const uint32_t lane_off = 2u * lane;
-    const SortSides sides = sort_sides<L>();  // the bank-median finish's sort
-    // Lane constants of the single-gain median groups: the bank-row mi of
-    // the lane's group, the LDS offset of its first value, its row, its first
-    // seed key and the mask of its value slots inside the bank.  Made once and
-    // kept (opaque copies): recomputed per frame they cost three quarter-rate
-    // multiplies and a 64-bit shift.  Group slot s = wave 64 / L + lane / L
-    // takes bank-row s, except that with the row step d = 4 (16-lane groups)
-    // the loaded rows go in blocks of 4 d, and the four groups of a wave take
-    // one bank of rows j, j + d, j + 2 d, j + 3 d of a block, so that their
-    // LDS reads fall in different banks; rows past the last whole block keep
-    // bank-row s.  Either way slot s is active exactly when s < BR.
-    int mi = 0, mrow = 0, moff = 0;
-    uint32_t mkey0 = 0, mvmask = 0;
-    if constexpr (!CMM && FLAT) {
-        const int grp = lane / L, gl = lane - grp * L;
-        mi = wave * (64 / L) + grp;
-        if (L == 16 && A.med_row_step == 4) {
-            constexpr int d = 4;
-            const int per = 4 * d * nb;                  // bank-rows of a block
-            if (mi < (R / (4 * d)) * per) {
-                const int blk = mi / per, t = mi - blk * per;
-                const int wi = t >> 2, g = t & 3;        // wave of the block, group
-                mi = (blk * 4 * d + wi % d + d * g) * nb + wi / d;
+    for (int v = 0; v < V; ++v)
+        if (8 * gl + slot_off<L, Q, R>(v, gl) < B) vmask |= 1u << v;
+    int mi_[P], o4_[P], own_[P];
+    bool wave_on[P];  // (uniform) the wave has a bank-row in this pass
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        mi_[p] = (p * kV2Waves + wave) * G + lane / L;
+        wave_on[p] = (p * kV2Waves + wave) * G < BR;
+        const bool act = mi_[p] < BR;
+        const int row = act ? mi_[p] / nb : 0;
+        o4_[p] = (act ? mi_[p] : 0) * B + 8 * gl;  // bank-rows follow one another
+        own_[p] = act && row >= own_lo && row < own_hi ? 1 : 0;
+        // opaque copies: kept in registers rather than recomputed per frame
+        asm volatile("" : "+v"(mi_[p]), "+v"(o4_[p]), "+v"(own_[p]));
+    }
+    asm volatile("" : "+v"(vmask));
+
+    // resident calibration of the lane's pixels
+    float pd[P][V], kk[P][V];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const float *const pp = A->ped + row_base + (uint32_t)o4_[p], *const kp = A->k + row_base + (uint32_t)o4_[p];
+        const bool quads = wave_on[p] && full;
+#pragma unroll
+        for (int v = 0; v < 8 * Q; v += 4) {
+            const int o = slot_off<L, Q, R>(v, gl);
+            f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = a;
+            if (quads) {
+                a = *reinterpret_cast<const f32x4_a8 *>(pp + o);
+                b = *reinterpret_cast<const f32x4_a8 *>(kp + o);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                pd[p][v + j] = a[j];
+                kk[p][v + j] = b[j];
             }
         }
-        const bool act = mi < BR;
-        mrow = act ? mi / nb : 0;
-        const int bank = act ? mi - mrow * nb : 0;
-        moff = mrow * W + bank * B + gl;
-        mkey0 = seed_key(mrow, bank, bank * B + gl);
-        const int lim = B - gl;
-        mvmask = B > L * (V - 1) ? ((L * (V - 1) < lim) ? (1u << V) - 1u : (1u << (V - 1)) - 1u)
-                                 : (uint32_t)((1ull << min(V, max(0, (lim + L - 1) / L))) - 1ull);
-        asm volatile("" : "+v"(mi), "+v"(mrow), "+v"(moff), "+v"(mkey0), "+v"(mvmask));
-    }
-    // this wave's bank-rows g < ng: bank-row index i = wave + 16g, its local
-    // row and its first pixel (offset from row_base), all wave-uniform
-    const int ng = BR > wave ? min(GMAX, (BR - wave + kV2Waves - 1) / kV2Waves) : 0;
-    int row_[GMAX], bank_[GMAX];
-    uint32_t gb_[GMAX];
 #pragma unroll
-    for (int g = 0; g < GMAX; ++g) {
-        const int i = wave + kV2Waves * g;
-        row_[g] = i / nb;
-        bank_[g] = i - row_[g] * nb;
-        gb_[g] = (uint32_t)row_[g] * W + (uint32_t)bank_[g] * B;
-    }
-
-    // resident calibration of this wave's bank-rows
-    float pd[GMAX][NQ][2], kk[GMAX][NQ][2];
-#pragma unroll
-    for (int g = 0; g < GMAX; ++g) {
-        const bool gv = g < ng;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            pd[g][q][0] = pd[g][q][1] = 0.0f;
-            kk[g][q][0] = kk[g][q][1] = 0.0f;
-            if (gv && lane_ok[q]) {
-                const uint32_t o = row_base + gb_[g] + 128 * q + lane_off;
-                const float2 pp = *reinterpret_cast<const float2 *>(A.ped + o);
-                const float2 kp = *reinterpret_cast<const float2 *>(A.k + o);
-                pd[g][q][0] = pp.x;
-                pd[g][q][1] = pp.y;
-                kk[g][q][0] = kp.x;
-                kk[g][q][1] = kp.y;
+        for (int v = 0; v < V; ++v) {
+            const int o = slot_off<L, Q, R>(v, gl);
+            if (v >= 8 * Q) pd[p][v] = kk[p][v] = 0.0f;
+            if (wave_on[p] && (v >= 8 * Q || !full) && ((vmask >> v) & 1u)) {
+                pd[p][v] = pp[o];
+                kk[p][v] = kp[o];
             }
-        }
-    }
-    // FLAT: the loaded rows are one contiguous block of R W words of each
-    // frame (W % 4 == 0), cut into 4-pixel chunks j = tid + 1024 c; each
-    // chunk's dark and 1/gain values stay in registers
-    const int nchunk = FLAT ? (R * W) >> 2 : 0;
-    float4 pdq[kFlatChunks], kkq[kFlatChunks];
-#pragma unroll
-    for (int c = 0; c < kFlatChunks; ++c) {
-        const int j = tid + kV2Threads * c;
-        pdq[c] = kkq[c] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (FLAT && j < nchunk) {
-            pdq[c] = *reinterpret_cast<const float4 *>(A.ped + row_base + 4u * j);
-            kkq[c] = *reinterpret_cast<const float4 *>(A.k + row_base + 4u * j);
         }
     }
     // the calibration loads complete here (vmcnt 0): left pending, their first
     // use inside the frame loop would make the compiler wait there for every
     // load in flight, the next frame's prefetch included
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    for (int x = tid; x < 2 * RN * 8; x += kV2Threads) s_bits[x] = 0;
+    for (int x = tid; x < 2 * RN * bw; x += kV2Threads) s_bits[x] = 0;
     for (int x = tid; x < 2 * RN; x += kV2Threads) s_cnt[x] = 0;
-    if (tid < 3) s_nseed[tid] = 0;
+    if (tid < 4) s_nseed[tid] = 0;
     if (tid < 2) s_hcnt[tid] = 0;
     if (tid == 0) s_photons = 0;
-    if (tid == 0) s_p2ctr = 0;
-    if (tid == 0) s_p4ctr = 0;
-
     if (tid == 0) s_chunk[0] = s_chunk[1] = 0;
-    uint32_t raw[GMAX][NQ];
-    auto load_raw = [&](uint64_t f, const bool(&lok)[NQ]) {
-        const uint32_t *fr = reinterpret_cast<const uint32_t *>(A.frames + f * npix + row_base);
+
+    // Raw words of a frame: Q 16-byte groups and R single words a lane (a load
+    // instruction's cost is the cache lines its lanes touch: with 8-byte groups
+    // a CSPAD frame's loads cost half as much again).  Not
+    // nontemporal: a line is shared by loads of neighbouring lane groups.  Where a
+    // bank ends inside the Q groups they are read as column pairs, each pair
+    // inside the bank or skipped.
+    u32x4 raw_[P][Q];
+    uint32_t rawt_[P][R > 0 ? R : 1];
 #pragma unroll
-        for (int g = 0; g < GMAX; ++g) {
-            const bool gv = g < ng;
+    for (int p = 0; p < P; ++p) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                // gb_[g] is even (W and B are), so the word address is a
-                // wave-uniform base plus the lane
-                raw[g][q] = (gv && lok[q]) ? __builtin_nontemporal_load(fr + ((gb_[g] >> 1) + 64 * q) + lane) : 0u;
+        for (int c = 0; c < Q; ++c) raw_[p][c] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int r = 0; r < (R > 0 ? R : 1); ++r) rawt_[p][r] = 0u;
+    }
+    const uint16_t *fr_next = A->frames + f_begin * npix + row_base;  // strip of the next frame to load
+    auto load_raw = [&](const uint16_t *fr, int o4, u32x4(&raw)[Q], uint32_t(&rawt)[R > 0 ? R : 1]) {
+        if (full) {
+#pragma unroll
+            for (int c = 0; c < Q; ++c)
+                raw[c] = *reinterpret_cast<const u32x4_a4 *>(fr + (uint32_t)o4 + 8 * L * c);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if ((vmask >> (8 * Q + r)) & 1u)
+                    rawt[r] = fr[(uint32_t)(o4 + slot_off<L, Q, R>(8 * Q + r, gl))];
+        } else {
+#pragma unroll
+            for (int c = 0; c < Q; ++c) {
+                const uint32_t *p = reinterpret_cast<const uint32_t *>(fr + (uint32_t)o4 + 8 * L * c);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if ((vmask >> (8 * c + 2 * j)) & 1u) raw[c][j] = p[j];
+            }
         }
     };
-    u32x2 rawq[kFlatChunks];
+    // the lane's values to and from LDS (an active group's, slots in the bank)
+    auto store_v = [&](const float(&x)[V], int o4) {
+        float *dst = s_v + o4;
+        if (full) {
 #pragma unroll
-    for (int c = 0; c < kFlatChunks; ++c) rawq[c] = u32x2{0u, 0u};
-    // (t: the thread index, an opaque copy made each frame, so that the
-    // chunk tests are recomputed rather than kept in scalar registers)
-    auto load_raw_flat = [&](uint64_t f, int t) {
-        const u32x2 *fr = reinterpret_cast<const u32x2 *>(A.frames + f * npix + row_base);
+            for (int c = 0; c < 2 * Q; ++c)
+                *reinterpret_cast<f32x4_a8 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
+                    f32x4{x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]};
 #pragma unroll
-        for (int c = 0; c < kFlatChunks; ++c) {
-            const int j = t + kV2Threads * c;
-            if (j < nchunk) rawq[c] = __builtin_nontemporal_load(fr + j);
+            for (int r = 0; r < R; ++r)
+                if ((vmask >> (8 * Q + r)) & 1u) dst[slot_off<L, Q, R>(8 * Q + r, gl)] = x[8 * Q + r];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 8 * Q; v += 2)
+                if ((vmask >> v) & 1u)
+                    *reinterpret_cast<float2 *>(dst + slot_off<L, Q, R>(v, gl)) = make_float2(x[v], x[v + 1]);
+        }
+    };
+    // Frames2 of the lane's pixels of frame f (own rows)
+    auto store_corrected = [&](uint32_t f, const float(&y)[V], int o4) {
+        float *dst = fresh(A)->corrected + f * npix + row_base + (uint32_t)o4;
+        if (full) {
+#pragma unroll
+            for (int c = 0; c < 2 * Q; ++c)
+                *reinterpret_cast<f32x4_a8 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
+                    f32x4{y[4 * c], y[4 * c + 1], y[4 * c + 2], y[4 * c + 3]};
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if ((vmask >> (8 * Q + r)) & 1u) dst[slot_off<L, Q, R>(8 * Q + r, gl)] = y[8 * Q + r];
+        } else {
+#pragma unroll
+            for (int v = 0; v < 8 * Q; v += 2)
+                if ((vmask >> v) & 1u)
+                    *reinterpret_cast<float2 *>(dst + slot_off<L, Q, R>(v, gl)) = make_float2(y[v], y[v + 1]);
         }
     };
     if (f_begin < f_end) {
-        if constexpr (FLAT)
-            load_raw_flat(f_begin, tid);
-        else
-            load_raw(f_begin, lane_ok);
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (wave_on[p]) load_raw(fr_next, o4_[p], raw_[p], rawt_[p]);
     }
     __syncthreads();
 
-    // Seeds of a bank-row held by an L-lane group in phase B (lane gl holds
-    // columns L v + gl in xs, +inf where absent or invalid): fl(x - m) > t,
-    // own rows only, appended to the pooled list sbuf (frame parity; order is
-    // free, phase 4 restores raster order) counted in slot (frame mod 3), with
-    // a DPP prefix of the lanes' counts and one LDS atomic per wave.  The test
-    // is the sign of fl(t - fl(x - m)) (see append_seeds_dense), and +inf is
-    // dropped by the sign of x - 2^100 (set for every finite value, which is
-    // far below 2^100).  All lanes of the wave must call it.
-    auto append_seeds = [&](const float(&xs)[V], float m, float t, bool own, int row, int bank, int gl, int sbuf,
-                            int slot) {
-        uint32_t sb = 0, fin = 0;
-#pragma unroll
-        for (int v = V - 1; v >= 0; --v) {
-            sb = __builtin_amdgcn_alignbit(sb, __float_as_uint(__fsub_rn(t, __fsub_rn(xs[v], m))), 31);
-            fin = __builtin_amdgcn_alignbit(fin, __float_as_uint(__fsub_rn(xs[v], 0x1p100f)), 31);
-        }
-        sb = own ? sb & fin : 0u;
-        const uint32_t ns = (uint32_t)__popc(sb);
-        const uint32_t incl = wave_incl_scan(ns);
-        const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        if (wtot) {
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&s_nseed[slot], wtot);
-            uint32_t pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + incl - ns;
-            while (sb) {
-                const int v = __ffs(sb) - 1;
-                sb &= sb - 1;
-                if (pos < (uint32_t)cap) s_seed[sbuf * cap + pos] = seed_key(row, bank, bank * B + L * v + gl);
-                ++pos;
-            }
-        }
-    };
-    // The same for the single-gain median kernels: values of the slots in
-    // vmask are finite (the others, past the bank, are dropped); a value is a
-    // seed when fl(x - m) > t, that is when fl(t - fl(x - m)) < 0 (exact
-    // difference of two finite values: its sign is the test, equality gives
-    // +0), one sign bit per value shifted in from the last value down.
-    auto append_seeds_dense = [&](const float(&xs)[V], float m, float t, bool own, uint32_t vmask, uint32_t key0,
-                                  int sbuf, int slot) {
+    // Seeds of the lane's bank-row: the slots in vm (inside the bank, own rows)
+    // with Frames2 above t, appended to the pooled list (order is free, phase 4
+    // restores raster order) and counted in `slot`, with a DPP prefix of the
+    // lanes' counts and one LDS atomic per wave.  The test is the sign of fl(t -
+    // v) (a nonzero difference of finite values keeps its sign, equality gives
+    // +0), one sign bit per value shifted in from the last value down.  All lanes
+    // of the wave must call it.
+    auto append_seeds = [&](const float(&xs)[V], float t, uint32_t vm, int slot, int o4) {
         uint32_t sb = 0;
 #pragma unroll
         for (int v = V - 1; v >= 0; --v)
-            sb = __builtin_amdgcn_alignbit(sb, __float_as_uint(__fsub_rn(t, __fsub_rn(xs[v], m))), 31);
-        sb = own ? sb & vmask : 0u;
+            sb = __builtin_amdgcn_alignbit(sb, __float_as_uint(__fsub_rn(t, xs[v])), 31);
+        sb &= vm;
         const uint32_t ns = (uint32_t)__popc(sb);
         const uint32_t incl = wave_incl_scan(ns);
         const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
@@ -702,23 +788,26 @@ __device__ __forceinline__ void frame_body(const V2Args &A, const int item)
             if (lane == 0) base = atomicAdd(&s_nseed[slot], wtot);
             uint32_t pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)base) + incl - ns;
             while (sb) {
-                const int v = __ffs(sb) - 1;
+                const int v = __builtin_ctz(sb);
                 sb &= sb - 1;
-                if (pos < (uint32_t)cap) s_seed[sbuf * cap + pos] = key0 + (uint32_t)(L * v);
+                if (pos < (uint32_t)cap) s_seed[pos] = (uint16_t)(o4 + slot_off<L, Q, R>(v, gl));
                 ++pos;
             }
         }
     };
 
-    // Software pipeline, two barriers per frame: iteration f runs
-    //   A: frame f's phase 1a, frame f-1's Frames2, frame f-2's phase 3 (one
-    //      wave, beside the others' 1a);
-    //   B: frame f's phase 1b with the seed list, then, claimed in chunks by
-    //      waves as they finish their median groups, frame f-1's phase 2
-    //      (which lists its hits) and frame f-2's phase 4 (over that list).
-    // Two more iterations drain it.  u, medians, seed lists, hit lists, hit
-    // bitmaps and counts are double-buffered by frame parity (par for f and
-    // f-2, pp for f-1); the seed counts are kept for three frames (f mod 3).
+    // Frame loop, two barriers per frame.  Iteration f:
+    //   A: the lanes correct frame f's words in registers (they were loaded a
+    //      frame ahead) and issue frame f+1's loads;
+    //   barrier 1: phase 2 of frame f-1 has read u for the last time;
+    //   B: each wave writes its bank-rows' u to LDS, finds their medians and
+    //      lists their seeds, with no other wave's data; one wave also runs
+    //      frame f-1's phase 3;
+    //   barrier 2: the seeds and u of frame f are complete;
+    //   C: frame f's phase 2 over the pooled seeds and frame f-1's phase 4 over
+    //      its hits, in chunks of 64, the first to the first waves and to the last
+    //      ones; waves without a chunk go on to A of the next frame.
+    // One more iteration drains it.
 #ifdef PDC_PHASE_TIMERS
     unsigned long long tm_prev = __builtin_amdgcn_s_memtime();
 #define PDC_PHASE(ph)                                                                     \
@@ -730,401 +819,261 @@ __device__ __forceinline__ void frame_body(const V2Args &A, const int item)
 #else
 #define PDC_PHASE(ph)
 #endif
-    // f mod 3, advanced with f (a 64-bit remainder per frame costs scalar
-    // instructions and registers)
-    int f3 = (int)(f_begin % 3);
-    for (uint64_t f = f_begin; f < f_end + 2; ++f, f3 = f3 == 2 ? 0 : f3 + 1) {
+    for (uint32_t f = f_begin; f < f_end + 1; ++f) {
+        // the slot tests are recomputed each frame from an opaque copy of the
+        // mask: hoisted out of the loop they would be kept in scalar registers,
+        // which this kernel does not have to spare
+        asm volatile("" : "+v"(vmask));
+#pragma unroll
+        for (int p = 0; p < P; ++p) asm volatile("" : "+v"(o4_[p]));
+        fr_next += npix;  // frame f + 1's strip
         const bool cur_ok = f < f_end;
-        const bool p1_ok = f >= f_begin + 1 && f - 1 < f_end;
-        const bool p2_ok = f >= f_begin + 2;
+        const bool p1_ok = f > f_begin;
         const int par = (int)(f & 1), pp = par ^ 1;
-        const int sc0 = f3, sc1 = f3 == 0 ? 2 : f3 - 1, sc2 = f3 == 2 ? 0 : f3 + 1;  // seed counts of f, f-1, f-2
-        const uint32_t nseed_1 = p1_ok ? s_nseed[sc1] : 0u;  // frame f-1
-        const uint32_t nseed_2 = p2_ok ? s_nseed[sc2] : 0u;  // frame f-2
-        const uint32_t nhit_2 = p2_ok ? s_hcnt[par] : 0u;    // frame f-2's listed hits
-        // a seed list or a hit list that was full: the general kernel redoes the unit
-        const bool ovf_1 = nseed_1 > (uint32_t)cap;
-        const bool ovf_2 = nseed_2 > (uint32_t)cap || nhit_2 > (uint32_t)hcap;
-        float *u_c = s_u + par * RW;
-        const float *u_p = s_u + pp * RW;
-        float *med_c = s_med + par * RN;
-        const float *med_p = s_med + pp * RN;
-        // the lane masks are recomputed each frame from an opaque copy of the
-        // lane offset: hoisted out of the loop they would be kept in scalar
-        // registers, which this kernel does not have to spare
-        bool lok[NQ];
-        {
-            uint32_t lo = lane_off;
-            asm volatile("" : "+v"(lo));
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) lok[q] = 128u * q + lo < (uint32_t)B;
-        }
-        int tid_f = tid;  // the same for the flat chunk tests
-        asm volatile("" : "+v"(tid_f));
+        const int sc0 = (int)(f & 3), sc1 = (int)((f + 3) & 3);  // seed counts of f, f-1
 
-        // ================= A: 1a(f) | Frames2(f-1) | 3(f-2) =======================
-        if (FLAT && cur_ok) {
-            // frame f's words were loaded at the end of the previous A
-#pragma unroll
-            for (int c = 0; c < kFlatChunks; ++c) {
-                const int j = tid_f + kV2Threads * c;
-                if (j < nchunk) {
-                    const uint32_t w0 = rawq[c].x & 0x3FFF3FFFu, w1 = rawq[c].y & 0x3FFF3FFFu;
-                    float4 o;
-                    o.x = __fmul_rn(__fsub_rn((float)(w0 & 0xFFFFu), pdq[c].x), kkq[c].x);
-                    o.y = __fmul_rn(__fsub_rn((float)(w0 >> 16), pdq[c].y), kkq[c].y);
-                    o.z = __fmul_rn(__fsub_rn((float)(w1 & 0xFFFFu), pdq[c].z), kkq[c].z);
-                    o.w = __fmul_rn(__fsub_rn((float)(w1 >> 16), pdq[c].w), kkq[c].w);
-                    *reinterpret_cast<float4 *>(u_c + 4 * j) = o;
-                }
-            }
-        }
-        if (!FLAT && cur_ok) {
-            uint32_t cur[GMAX][NQ];
-#pragma unroll
-            for (int g = 0; g < GMAX; ++g)
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) cur[g][q] = raw[g][q];
-            if (f + 1 < f_end) load_raw(f + 1, lok);
+        // ================= A: correction of frame f in registers =================
+        float x[V];
+        uint32_t slow = 0;  // auto-ranging: slots not in range 0
+        auto correct = [&](int p) {
+            const u32x4(&raw)[Q] = raw_[p];
+            const uint32_t(&rawt)[R > 0 ? R : 1] = rawt_[p];
             if constexpr (!MG) {
 #pragma unroll
-                for (int g = 0; g < GMAX; ++g)
+                for (int c = 0; c < Q; ++c)
 #pragma unroll
-                    for (int q = 0; q < NQ; ++q)
-                        if (g < ng && lok[q])
-                            *reinterpret_cast<float2 *>(u_c + gb_[g] + 128 * q + lane_off) =
-                                make_float2(dark_gain(cur[g][q] & 0xFFFFu, pd[g][q][0], kk[g][q][0]),
-                                            dark_gain(cur[g][q] >> 16, pd[g][q][1], kk[g][q][1]));
+                    for (int j = 0; j < 4; ++j) {
+                        const int v = 8 * c + 2 * j;
+                        const uint32_t w = raw[c][j] & 0x3FFF3FFFu;
+                        x[v] = __fmul_rn(__fsub_rn(cvt_lo16(w), pd[p][v]), kk[p][v]);
+                        x[v + 1] = __fmul_rn(__fsub_rn(cvt_hi16(w), pd[p][v + 1]), kk[p][v + 1]);
+                    }
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[8 * Q + r] = dark_gain(rawt[r], pd[p][8 * Q + r], kk[p][8 * Q + r]);
             } else {
-                // auto-ranging: range 0 from the resident planes and invalid
-                // codes as +inf (counted on own rows) first; the rarer pixels in
-                // ranges 1 and 2 then read their planes from memory
-                uint32_t ninv = 0, slow = 0;  // slow: bit 2 (g NQ + q) + h for ranges 1, 2
+                // range 0 from the resident planes; the other pixels (an invalid
+                // code, or the rarer ranges 1 and 2) leave their raw word here as
+                // bits and are finished in B
+                slow = 0;
 #pragma unroll
-                for (int g = 0; g < GMAX; ++g)
-#pragma unroll
-                    for (int q = 0; q < NQ; ++q)
-                        if (g < ng && lok[q]) {
-                            const uint32_t w = cur[g][q];
-                            const int r0 = gain_range(w & 0xFFFFu, A.gain_mode), r1 = gain_range(w >> 16, A.gain_mode);
-                            const float u0 = r0 == 0 ? dark_gain(w & 0xFFFFu, pd[g][q][0], kk[g][q][0]) : INFINITY;
-                            const float u1 = r1 == 0 ? dark_gain(w >> 16, pd[g][q][1], kk[g][q][1]) : INFINITY;
-                            *reinterpret_cast<float2 *>(u_c + gb_[g] + 128 * q + lane_off) = make_float2(u0, u1);
-                            if (row_[g] >= own_lo && row_[g] < own_hi) ninv += (uint32_t)(r0 < 0) + (uint32_t)(r1 < 0);
-                            slow |= ((uint32_t)(r0 > 0) | ((uint32_t)(r1 > 0) << 1)) << (2 * (g * NQ + q));
-                        }
-                while (slow) {
-                    const int bit = __ffs(slow) - 1;
-                    slow &= slow - 1;
-                    const int gq = bit >> 1, h = bit & 1;
-                    const int g = gq / NQ, q = gq - g * NQ;
-                    const uint32_t off = gb_[g] + 128 * q + lane_off + h;
-                    const uint32_t w = (cur[g][q] >> (16 * h)) & 0xFFFFu;
-                    const uint64_t o = row_base + off + (uint64_t)gain_range(w, A.gain_mode) * npix;
-                    u_c[off] = dark_gain(w, A.ped[o], A.k[o]);
+                for (int v = 0; v < V; ++v) {
+                    const uint32_t w = v < 8 * Q ? raw[v < 8 * Q ? v / 8 : 0][(v & 7) / 2] : rawt[v < 8 * Q ? 0 : v - 8 * Q];
+                    const uint32_t h = v < 8 * Q && (v & 1) ? w >> 16 : w & 0xFFFFu;
+                    const float u = dark_gain(h, pd[p][v], kk[p][v]);
+                    const bool r0 = h < 0x4000u;
+                    x[v] = r0 ? u : __uint_as_float(h);
+                    slow |= (uint32_t)!r0 << v;
                 }
-                const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(ninv), 63);
-                if (lane == 0 && tot) atomicAdd(A.invalid + f, tot);
+                slow &= vmask;
             }
-        }
-        // frame f-1's hit bitmaps and counts (parity pp) are rebuilt by its
-        // local maxima in B; their last reader, frame f-3, finished in B of f-1
-        if (p1_ok) {
-            for (int x = tid; x < RN * 8; x += kV2Threads) s_bits[pp * RN * 8 + x] = 0;
-            for (int x = tid; x < RN; x += kV2Threads) s_cnt[pp * RN + x] = 0;
+            if (f + 1 < f_end) load_raw(fr_next, o4_[p], raw_[p], rawt_[p]);
+            if constexpr (!MG) {
+                // columns past the bank
+                if (!full) {
+#pragma unroll
+                    for (int v = 0; v < 8 * Q; ++v) x[v] = (vmask >> v) & 1u ? x[v] : INFINITY;
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[8 * Q + r] = (vmask >> (8 * Q + r)) & 1u ? x[8 * Q + r] : INFINITY;
+            }
+        };
+        if (cur_ok && wave_on[0]) correct(0);
+        PDC_PHASE(0);
+        lds_barrier();  // 1
+        PDC_PHASE(1);
+
+        // ================= B: 1(f), one wave 3(f-1) ==============================
+        const uint32_t nseed_1 = p1_ok ? s_nseed[sc1] : 0u;  // frame f-1's seeds and listed hits
+        const uint32_t nhit_1 = p1_ok ? s_hcnt[pp] : 0u;
+        // a seed list or a hit list that was full: the general kernel redoes the unit
+        const bool ovf_1 = nseed_1 > (uint32_t)cap || nhit_1 > (uint32_t)hcap;
+        // frame f's hit bitmaps and counts (parity par) are rebuilt by its local
+        // maxima in C; their last reader was frame f-2's phase 4 in C of f-1
+        if (cur_ok) {
+            for (int j = tid; j < RN * bw; j += kV2Threads) s_bits[par * RN * bw + j] = 0;
+            for (int j = tid; j < RN; j += kV2Threads) s_cnt[par * RN + j] = 0;
         }
         if (tid == 0) {
-            s_nseed[sc0] = 0;  // frame f-3's count, last read before B of f-1
-            s_hcnt[pp] = 0;    // frame f-3's hits were written in B of f-1
-            *s_p2next = 0;
-            *s_p4next = 0;
+            s_nseed[(sc0 + 1) & 3] = 0;  // frame f+1's (last used by frame f-3)
+            s_hcnt[par] = 0;
         }
-        if (KEEP && !FLAT && p1_ok) {
-            // Frames2 of frame f-1 (its u and medians, parity pp, are intact);
-            // the flat kernels write Frames2 in phase B
-#pragma unroll
-            for (int g = 0; g < GMAX; ++g) {
-                if (g >= ng) break;
-                const int i = wave + kV2Waves * g;
-                const int row = row_[g];
-                if (row >= own_lo && row < own_hi) {
-                    const float m = uniform_f(med_p[i]);
-#pragma unroll
-                    for (int q = 0; q < NQ; ++q)
-                        if (lok[q]) {
-                            const float2 u2 = *reinterpret_cast<const float2 *>(u_p + gb_[g] + 128 * q + lane_off);
-                            *reinterpret_cast<float2 *>(A.corrected + (f - 1) * npix + row_base + gb_[g] + 128 * q +
-                                                        lane_off) = make_float2(__fsub_rn(u2.x, m), __fsub_rn(u2.y, m));
-                        }
-                }
-            }
-        }
-        if (p2_ok && wave == kP3Wave) {
-            // bank-row prefix of frame f-2's hit counts (parity par), staging
-            // chunk claim; the wave that runs it issues first, so it also
-            // finishes its own phase 1a first
-            uint32_t total = 0;
-            if (!ovf_2) {
-                for (int b0 = 0; b0 < BR; b0 += 64) {
-                    const int i = b0 + lane;
-                    const uint32_t c = i < BR ? s_cnt[par * RN + i] : 0u;
-                    const uint32_t incl = wave_incl_scan(c);
-                    if (i < BR) s_pref[i] = total + incl - c;
-                    total += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-                }
-            }
+        if (p1_ok && wave == kP3Wave) {
+            // staging chunk claim for frame f-1's hits
+            const uint32_t total = ovf_1 ? 0u : nhit_1;
             if (lane == 0) {
+                const V2ArgsK K = fresh(A);
                 // the chunk lives in LDS: in registers it would be spilled to
                 // scratch, whose reload waits for the frame prefetch
                 uint64_t chunk_cur = s_chunk[0], chunk_end = s_chunk[1];
-                const uint64_t unit = (f - 2) * (uint64_t)A.n_strips + strip;
+                const uint64_t unit = (uint64_t)(f - 1) * K->n_strips + strip;
                 uint64_t base = chunk_cur;
-                if (ovf_2) {
-                    // the seed list was full: the general kernel redoes this unit
-                    atomicOr(&A.state->fallback, 1u);
-                    if (A.fb_units) A.fb_units[atomicAdd(&A.state->n_fallback, 1ull)] = unit;
+                if (ovf_1) {
+                    // a list was full: the general kernel redoes this unit
+                    atomicOr(&K->state->fallback, 1u);
+                    if (K->fb_units) K->fb_units[atomicAdd(&K->state->n_fallback, 1ull)] = unit;
                     base = kNoBase;
                 } else if (total > 0) {
                     if (chunk_cur + total > chunk_end) {
                         const uint64_t sz = total > kChunkHits ? (uint64_t)total : kChunkHits;
-                        chunk_cur = atomicAdd(&A.state->cursor, (unsigned long long)sz);
+                        chunk_cur = atomicAdd(&K->state->cursor, (unsigned long long)sz);
                         chunk_end = chunk_cur + sz;
                     }
-                    if (chunk_cur + total <= A.pool_cap) {
+                    if (chunk_cur + total <= K->pool_cap) {
                         base = chunk_cur;
                         chunk_cur += total;
                     } else {
                         base = kNoBase;
-                        atomicOr(&A.state->overflow, 1u);
+                        atomicOr(&K->state->overflow, 1u);
                     }
                 }
-                A.unit_base[unit] = base;
-                A.unit_count[unit] = total;
-                A.unit_photons[unit] = s_photons;  // frame f-2's, summed in B of f-1
+                K->unit_base[unit] = base;
+                K->unit_count[unit] = total;
+                K->unit_photons[unit] = s_photons;  // frame f-1's, summed in its C
                 s_photons = 0;
                 s_base = base;
                 s_chunk[0] = chunk_cur;
                 s_chunk[1] = chunk_end;
             }
         }
-        // the loads of frame f + 1 go out last in A, into the registers frame
-        // f's words were in: they overlap phase B and the barriers, and no
-        // wait in A (the staging claim's atomics) waits for them
-        if (FLAT && f + 1 < f_end) load_raw_flat(f + 1, tid_f);
-        PDC_PHASE(0);
-        lds_barrier();  // A -> B
-        PDC_PHASE(1);
-
-        // ================= B: 1b(f) | 2(f-1) | 4(f-2) =============================
-        if (CMM && cur_ok && A.cm_mode == 1) {
-            // thresholded mean of each bank-row (Fig. c), stacked stages: the sum
-            // of the noise values is exact, rounded once (the group's lanes add
-            // two binary64 limbs); v replaces u in place and the median slot
-            // holds 0.  A bank-row whose values span more than two limbs hold
-            // marks the frame's seed list full, so that the general kernel
-            // redoes the unit from the separately computed stage values.
-            constexpr int G = 64 / L;
-            const int grp = lane / L, gl = lane - grp * L;
-            const int i = wave * G + grp;
-            const bool act = i < BR;
-            const int row = act ? i / nb : 0;
-            const int bank = act ? i - row * nb : 0;
-            float *dst = u_c + row * W + bank * B;
-            float x[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const int c = L * v + gl;
-                x[v] = (act && c < B) ? dst[c] : INFINITY;  // +inf: absent or invalid, never noise
-            }
-            SumWindow win = {A.sum_lo, A.sum_hi};
-            bool wide = false;
-#pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                if (s >= A.cm_stages) break;
-                int n;
-                bool fits;
-                const float sum = region_sum<L, V, false>(x, A.t_cm, (uint32_t)B, win, n, fits);
-                wide |= !fits;
-                const int n0 = gsum_i<L>(n);
-                const float cm = __fdiv_rn(sum, fmaxf((float)n0, A.cm_guard));
-                win = next_window(win, cm);
-#pragma unroll
-                for (int v = 0; v < V; ++v) x[v] = __fsub_rn(x[v], cm);
-            }
-            if (act && wide && gl == 0) atomicAdd(&s_nseed[sc0], (uint32_t)cap + 1u);
-            if (act) {
-                float *f2 = (KEEP && FLAT && row >= own_lo && row < own_hi)
-                                ? A.corrected + f * npix + row_base + row * W + bank * B
-                                : nullptr;
+        for (int p = 0; p < P; ++p) {
+            if (!cur_ok || !wave_on[p]) continue;
+            if (p > 0) correct(p);
+            const int o4 = o4_[p], mi = mi_[p];
+            const bool act = mi < BR, own = own_[p] != 0;
+            uint32_t bad = 0;  // slots with an invalid code
+            uint32_t vm = own ? vmask : 0u;  // slots that may be seeds
+            if constexpr (MG) {
+                // ranges 1 and 2: the raw word waits in the pixel's u slot
+                if (act) store_v(x, o4);
+                if (!act) slow = 0;
+                uint32_t todo = slow;
+                while (todo) {
+                    const int v = __builtin_ctz(todo);
+                    todo &= todo - 1u;
+                    const int off = o4 + slot_off<L, Q, R>(v, gl);
+                    const uint32_t w = __float_as_uint(s_v[off]);
+                    const int rg = gain_range(w, A->gain_mode);
+                    float u = INFINITY;
+                    if (rg < 0) {
+                        bad |= 1u << v;
+                    } else {
+                        const uint64_t o = row_base + (uint32_t)off + (uint64_t)rg * npix;
+                        u = dark_gain(w, A->ped[o], A->k[o]);
+                    }
+                    s_v[off] = u;
+                }
+                const uint32_t ninv = own ? (uint32_t)__popc(bad) : 0u;
+                const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(ninv), 63);
+                if (lane == 0 && tot) atomicAdd(fresh(A)->invalid + f, tot);
+                // the lane wrote these words itself
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    const int c = L * v + gl;
-                    if (c < B) {
-                        const float y = x[v] < INFINITY ? x[v] : 0.0f;  // invalid: v = 0
-                        dst[c] = y;
-                        if (f2) f2[c] = y;
-                    }
+                    const float t = s_v[o4 + slot_off<L, Q, R>(v, gl)];
+                    x[v] = (vmask >> v) & 1u ? t : INFINITY;
                 }
-                if (gl == 0) med_c[i] = 0.0f;
+                vm &= ~bad;
             }
-            append_seeds(x, 0.0f, A.t_seed, act && row >= own_lo && row < own_hi, row, bank, gl, par, sc0);
-        }
-        if (CMM && cur_ok && A.cm_mode == 2) {
-            // thresholded-mean common mode, computed ahead: v = ((u - c1) - c2) - c3
-            // replaces u in place and the bank-row's median slot holds 0
-            constexpr int G = 64 / L;
-            const int grp = lane / L, gl = lane - grp * L;
-            const int i = wave * G + grp;
-            const bool act = i < BR;
-            const int row = act ? i / nb : 0;
-            const int bank = act ? i - row * nb : 0;
-            float x[V];
+            if constexpr (CMM != 0) {
+                // thresholded mean (Fig. c)
+                if constexpr (CMM == 1) {
+                    // the bank-row's stacked stages: the sum of the noise values
+                    // is exact, rounded once (the group's lanes add two binary64
+                    // limbs).  A bank-row whose values span more than two limbs
+                    // hold marks the frame's seed list full, so that the general
+                    // kernel redoes the unit from the separately computed values.
+                    SumWindow win = {A->sum_lo, A->sum_hi};
+                    bool wide = false;
 #pragma unroll
-            for (int v = 0; v < V; ++v) x[v] = INFINITY;
-            if (act) {
-                const uint32_t grow = (uint32_t)(lr0 + row);  // global row
-                const uint32_t reg = A.cm_tile ? grow / (uint32_t)H : grow * (uint32_t)nb + bank;
-                const float *cv = A.cm + (f * A.cm_regions + reg) * 3;
-                const float c0 = cv[0], c1 = cv[1], c2 = cv[2];
-                float *dst = u_c + row * W + bank * B;
-                float *f2 = (KEEP && FLAT && row >= own_lo && row < own_hi)
-                                ? A.corrected + f * npix + row_base + row * W + bank * B
-                                : nullptr;
+                    for (int s = 0; s < 3; ++s) {
+                        if (s >= A->cm_stages) break;
+                        int n;
+                        bool fits;
+                        const float sum = region_sum<L, V, false>(x, A->t_cm, (uint32_t)B, win, n, fits);
+                        wide |= !fits;
+                        const int n0 = gsum_i<L>(n);
+                        const float cm = __fdiv_rn(sum, fmaxf((float)n0, A->cm_guard));
+                        win = next_window(win, cm);
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    const int c = L * v + gl;
-                    if (c < B) {
-                        const float u = dst[c];
-                        // an invalid pixel (+inf) becomes 0, so that v = 0
-                        const float y = __fsub_rn(__fsub_rn(__fsub_rn(u, c0), c1), c2);
-                        x[v] = y;
-                        dst[c] = (MG && !(u < INFINITY)) ? 0.0f : y;
-                        if (f2) f2[c] = y;
+                        for (int v = 0; v < V; ++v) x[v] = __fsub_rn(x[v], cm);
                     }
+                    if (act && wide && gl == 0) atomicAdd(&s_nseed[sc0], (uint32_t)cap + 1u);
+                } else {
+                    // stage values computed ahead: v = ((u - c1) - c2) - c3
+                    const uint32_t gi = (uint32_t)lr0 * nb + (uint32_t)(act ? mi : 0);  // bank-row of the frame
+                    const uint32_t reg = A->cm_tile ? gi / ((uint32_t)nb * (uint32_t)H) : gi;
+                    const float *cv = A->cm + ((uint64_t)f * A->cm_regions + reg) * 3;
+                    const float c0 = cv[0], c1 = cv[1], c2 = cv[2];
+#pragma unroll
+                    for (int v = 0; v < V; ++v) x[v] = __fsub_rn(__fsub_rn(__fsub_rn(x[v], c0), c1), c2);
                 }
-                if (gl == 0) med_c[i] = 0.0f;
-            }
-            append_seeds(x, 0.0f, A.t_seed, act && row >= own_lo && row < own_hi, row, bank, gl, par, sc0);
-        }
-        if (!CMM && FLAT && cur_ok && wave * (64 / L) < BR) {  // waves without a bank-row skip the search
-            const int gl = lane & (L - 1);
-            const bool act = mi < BR;
-            const float *src = u_c + moff;
-            // every lane reads (inside the u buffers or the LDS that follows
-            // them; an inactive group reads row 0) and columns past the bank
-            // become +inf; lim is opaque so that the compares stay at the
-            // reads rather than as loop-invariant masks
-            int lim = B - gl;
-            asm volatile("" : "+v"(lim));
-            const bool tail_only = B > L * (V - 1);
-            float x[V];
-            read_group<V, L>(x, src, lim, tail_only, INFINITY);
-            const float m = group_median<V, L, false>(x, src, B, kmed, A.rank_width, act, s_gs + tid, B, sides);
-            if (act && gl == 0) {
-                med_c[mi] = m;
+            } else {
+                if (!MG && act) store_v(x, o4);
+                int nv = B, kq = (B - 1) / 2;
+                bool actv = act;
+                if constexpr (MG) {
+                    // the median of the valid values only (invalid ones are +inf)
+                    nv = B - gsum_i<L>(__popc(bad));
+                    kq = nv > 0 ? (nv - 1) / 2 : 0;
+                    actv = act && nv > 0;
+                }
+                // finish scratch: the frame's own hit list, unused until C
+                float *gsc = lds + Ly.hl + par * Ly.hl_stride + (wave * G + lane / L) * (S * L);
+                float m = group_median<L, Q, R, S, MG>(x, s_v + o4, nv, kq, A->rank_width, actv, gsc, full, sides);
+                if (MG && !actv) m = 0.0f;
                 // kept for patches: the own rows' medians (each row has one owner)
-                if (A.meds && mrow >= own_lo && mrow < own_hi)
-                    A.meds[f * ((uint64_t)A.T * A.H * nb) + (uint64_t)lr0 * nb + (uint32_t)mi] = m;
-            }
-            const bool own = act && mrow >= own_lo && mrow < own_hi;
-            if (KEEP && own) {
-                float *f2 = A.corrected + f * npix + row_base + moff;
+                if (float *const meds = fresh(A)->meds)
+                    if (own && gl == 0)
+                        meds[f * ((uint64_t)fresh(A)->T * H * nb) + (uint64_t)lr0 * nb + (uint32_t)mi] = m;
 #pragma unroll
-                for (int v = 0; v < V; ++v)
-                    if (L * v < lim) f2[L * v] = __fsub_rn(x[v], m);
+                for (int v = 0; v < V; ++v) x[v] = __fsub_rn(x[v], m);
             }
+            // x holds Frames2 now; an invalid pixel's value is +0
+            if constexpr (MG) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) x[v] = x[v] < INFINITY ? x[v] : 0.0f;
+            }
+            if (act) store_v(x, o4);
+            if (KEEP && own) store_corrected(f, x, o4);
             PDC_PHASE(2);
-            // slots past the bank (+inf) are no seeds
-            append_seeds_dense(x, m, A.t_seed, own, mvmask, mkey0, par, sc0);
-        }
-        if (!CMM && !FLAT && cur_ok && wave * (64 / L) < BR) {  // waves without a bank-row skip the search
-            constexpr int G = 64 / L;
-            const int grp = lane / L, gl = lane - grp * L;
-            const int i = wave * G + grp;
-            const bool act = i < BR;
-            const int row = act ? i / nb : 0;
-            const int bank = act ? i - row * nb : 0;
-            const float *src = u_c + row * W + bank * B;
-            // every lane reads (inside the u buffers or the LDS that follows
-            // them; an inactive group reads row 0) and columns past the bank
-            // become +inf; lim is opaque so that the compares stay here
-            // rather than as loop-invariant masks
-            int lim = B - gl;
-            asm volatile("" : "+v"(lim));
-            float x[V];
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const float t = src[L * v + gl];
-                x[v] = L * v < lim ? t : INFINITY;
-            }
-            int nv = B, kq = kmed;
-            bool actv = act;
-            if constexpr (MG) {
-                // the median of the valid values only (invalid ones are +inf)
-                int nl = 0;
-#pragma unroll
-                for (int v = 0; v < V; ++v) nl += x[v] < INFINITY ? 1 : 0;
-                nv = gsum_i<L>(nl);
-                kq = nv > 0 ? (nv - 1) / 2 : 0;
-                actv = act && nv > 0;
-            }
-            float m = group_median<V, L, MG>(x, src + gl, nv, kq, A.rank_width, actv, s_gs + tid, B, sides);
-            if constexpr (MG) {
-                if (!actv) m = 0.0f;
-                // invalid pixels take the median: v = fl(m - m) = +0
-                if (act) {
-                    float *dst = u_c + row * W + bank * B;
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const int c = L * v + gl;
-                        if (c < B && !(x[v] < INFINITY)) dst[c] = m;
-                    }
-                }
-            }
-            if (act && gl == 0) {
-                med_c[i] = m;
-                // kept for patches: the own rows' medians (each row has one owner)
-                if (A.meds && row >= own_lo && row < own_hi)
-                    A.meds[f * ((uint64_t)A.T * A.H * nb) + (uint64_t)(lr0 + row) * nb + bank] = m;
-            }
-            append_seeds(x, m, A.t_seed, act && row >= own_lo && row < own_hi, row, bank, gl, par, sc0);
+            append_seeds(x, A->t_seed, vm, sc0, o4);
         }
         PDC_PHASE(3);
-        if (p1_ok && !ovf_1) {
-            // frame f-1's seeds in chunks of 64, claimed by whole waves as they
-            // finish their median groups (waves without groups start at once)
+        lds_barrier();  // 2
+        PDC_PHASE(4);
+
+        // ================= C: 2(f), 4(f-1) =======================================
+        // few waves have work here and all the others wait for them at barrier 1
+        __builtin_amdgcn_s_setprio(3);
+        const uint32_t nseed_0 = cur_ok ? s_nseed[sc0] : 0u;
+        if (nseed_0 <= (uint32_t)cap) {
+            // frame f's seeds
             unsigned long long my_ph = 0;
-            for (;;) {
-                uint32_t c0 = 0;
-                if (lane == 0) c0 = atomicAdd(s_p2next, 64u);
-                c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c0);
-                if (c0 >= nseed_1) break;
+            float *hq = lds + Ly.hl + par * Ly.hl_stride;
+            uint16_t *hp = reinterpret_cast<uint16_t *>(hq + hcap);
+            for (uint32_t c0 = 64u * (uint32_t)wave; c0 < nseed_0; c0 += 64u * kV2Waves) {
                 const uint32_t j = c0 + lane;
-                if (j < nseed_1) {
-                    const uint32_t key = s_seed[pp * cap + j];
-                    const int row = (int)(key >> 18), bank = (int)((key >> 11) & 127u), col = (int)(key & 2047u);
-                    const int i = row * nb + bank;
-                    const int cb = col - bank * B;
+                if (j < nseed_0) {
+                    const uint32_t at = s_seed[j];
+                    const int row = (int)(__umul24(at, A->row_mul) >> A->row_sh), col = (int)(at - __umul24(row, W));
                     // the 3x3 neighbourhood from the row above and the column
-                    // left; the left and right columns take the next bank's
-                    // median at a bank edge.  Neighbours outside the loaded
-                    // rows, across a tile edge or outside the row are -inf:
-                    // never above the seed nor above t_nb.
-                    const float *up = u_p + (row - 1) * W + (col - 1);
-                    const float *mp = med_p + (row - 1) * nb + bank;
-                    const int ml = cb == 0 ? -1 : 0, mr = cb == B - 1 ? 1 : 0;
-                    const bool r0 = row >= 1 && row != bnd, r2 = row + 1 < R && row + 1 != bnd;
-                    const bool c0 = col >= 1, c2 = col + 1 < W;
+                    // left.  Neighbours outside the loaded rows, across a tile
+                    // edge or outside the row are -inf: never above the seed nor
+                    // above t_nb.
+                    const float *up = s_v + (int)at - W - 1;
                     float nv[3][3];
 #pragma unroll
+                    for (int dr = 0; dr < 3; ++dr)
+#pragma unroll
+                        for (int dc = 0; dc < 3; ++dc) nv[dr][dc] = up[dr * W + dc];
+                    const bool r0 = row >= 1 && row != bnd, r2 = row + 1 < nrow && row + 1 != bnd;
+                    const bool c0ok = col >= 1, c2ok = col + 1 < W;
+#pragma unroll
                     for (int dr = 0; dr < 3; ++dr) {
-                        const float m0 = mp[dr * nb + ml], m1 = mp[dr * nb], m2 = mp[dr * nb + mr];
                         const bool rin = dr == 1 || (dr == 0 ? r0 : r2);
-                        const float a = __fsub_rn(up[dr * W], m0), b = __fsub_rn(up[dr * W + 1], m1),
-                                    c = __fsub_rn(up[dr * W + 2], m2);
-                        nv[dr][0] = rin && c0 ? a : -INFINITY;
-                        nv[dr][1] = rin ? b : -INFINITY;
-                        nv[dr][2] = rin && c2 ? c : -INFINITY;
+                        nv[dr][0] = rin && c0ok ? nv[dr][0] : -INFINITY;
+                        nv[dr][1] = rin ? nv[dr][1] : -INFINITY;
+                        nv[dr][2] = rin && c2ok ? nv[dr][2] : -INFINITY;
                     }
                     const float vp = nv[1][1];
                     // strictly above the neighbours before it in raster order,
@@ -1132,54 +1081,99 @@ __device__ __forceinline__ void frame_body(const V2Args &A, const int item)
                     const float me = fmaxf(fmaxf(nv[0][0], nv[0][1]), fmaxf(nv[0][2], nv[1][0]));
                     const float ml2 = fmaxf(fmaxf(nv[1][2], nv[2][0]), fmaxf(nv[2][1], nv[2][2]));
                     const bool is_max = vp > me && vp >= ml2;
+                    const uint64_t hm = __ballot(is_max);
                     if (is_max) {
+                        const int bank = (int)(__umul24(col, A->bank_mul) >> kBankShift);
+                        const int i = (int)__umul24(row, nb) + bank;
+                        const int cb = col - (int)__umul24(bank, B);
+                        const int first = __builtin_ctzll(hm);
+                        uint32_t hbase = 0;
+                        if (lane == first) hbase = atomicAdd(&s_hcnt[par], (uint32_t)__popcll(hm));
+                        hbase = (uint32_t)__builtin_amdgcn_readfirstlane((int)hbase);
                         float qsum = 0.0f;
 #pragma unroll
                         for (int dr = 0; dr < 3; ++dr)
 #pragma unroll
                             for (int dc = 0; dc < 3; ++dc)
-                                qsum = __fadd_rn(qsum, nv[dr][dc] > A.t_nb ? nv[dr][dc] : 0.0f);
-                        atomicOr(&s_bits[(pp * RN + i) * 8 + (cb >> 5)], 1u << (cb & 31));
-                        atomicAdd(&s_cnt[pp * RN + i], 1u);
-                        my_ph += photon_count(qsum, A.photon_adu);
+                                qsum = __fadd_rn(qsum, nv[dr][dc] > A->t_nb ? nv[dr][dc] : 0.0f);
+                        atomicOr(&s_bits[__umul24(par * RN + i, bw) + (cb >> 5)], 1u << (cb & 31));
+                        atomicAdd(&s_cnt[par * RN + i], 1u);
+                        my_ph += photon_count(qsum, A->photon_adu);
                         // the hit list (any order; past its end the unit is redone)
-                        const uint32_t h = atomicAdd(&s_hcnt[pp], 1u);
-                        if (h < (uint32_t)hcap) s_hl[pp * hcap + h] = make_uint2(key, __float_as_uint(qsum));
+                        const uint32_t h = hbase + (uint32_t)mbcnt(hm);
+                        if (h < (uint32_t)hcap) {
+                            hq[h] = qsum;
+                            hp[h] = (uint16_t)at;
+                        }
                     }
                 }
             }
-            if (my_ph) atomicAdd(&s_photons, my_ph);
-        }
-        PDC_PHASE(4);
-        if (p2_ok && !ovf_2) {
-            // frame f-2's hits in raster position (bank-row prefix + hits left
-            // of the hit in its bank-row), claimed in chunks of 64 like phase 2
-            const uint64_t base = s_base;
-            if (base != kNoBase) {
-                for (;;) {
-                    uint32_t c0 = 0;
-                    if (lane == 0) c0 = atomicAdd(s_p4next, 64u);
-                    c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)c0);
-                    if (c0 >= nhit_2) break;
-                    const uint32_t j = c0 + lane;
-                    if (j < nhit_2) {
-                        const uint2 e = s_hl[par * hcap + j];
-                        const uint32_t key = e.x;
-                        const int row = (int)(key >> 18), bank = (int)((key >> 11) & 127u), col = (int)(key & 2047u);
-                        const int i = row * nb + bank;
-                        const int cb = col - bank * B;
-                        const uint32_t *bw = s_bits + (par * RN + i) * 8;
-                        uint32_t rank = 0;
-                        for (int w = 0; w < (cb >> 5); ++w) rank += __popc(bw[w]);
-                        rank += __popc(bw[cb >> 5] & ((1u << (cb & 31)) - 1u));
-                        const uint32_t pix = row_base + (uint32_t)row * W + col;
-                        A.pool[base + s_pref[i] + rank] = make_uint2(pix, e.y);
-                    }
+            // the wave's photons: 32-bit sums when every lane's is small (64 of
+            // them then fit), else lane by lane
+            if (__ballot(my_ph != 0)) {
+                if (__ballot(my_ph >> 26) == 0) {
+                    const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan((uint32_t)my_ph), 63);
+                    if (lane == 0) atomicAdd(&s_photons, (unsigned long long)sum);
+                } else if (my_ph) {
+                    atomicAdd(&s_photons, my_ph);
                 }
             }
         }
         PDC_PHASE(5);
-        lds_barrier();  // B -> next A
+        if (p1_ok && !ovf_1 && nhit_1) {
+            // frame f-1's hits in raster position (bank-row prefix + hits left
+            // of the hit in its bank-row)
+            const uint64_t base = s_base;
+            uint32_t c0 = 64u * (uint32_t)(kV2Waves - 1 - wave);
+            if (base != kNoBase && c0 < nhit_1) {
+                const float *hq = lds + Ly.hl + pp * Ly.hl_stride;
+                const uint16_t *hp = reinterpret_cast<const uint16_t *>(hq + hcap);
+                uint2 *const pool = fresh(A)->pool;
+                // bank-row prefix of the hit counts: bank-row 64 k + lane in pref[k]
+                uint32_t pref[kCntRegs], run = 0;
+#pragma unroll
+                for (int k = 0; k < kCntRegs; ++k) {
+                    const int i = 64 * k + lane;
+                    const uint32_t c = i < BR ? s_cnt[pp * RN + i] : 0u;
+                    const uint32_t incl = wave_incl_scan(c);
+                    pref[k] = run + incl - c;
+                    run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                }
+                for (; c0 < nhit_1; c0 += 64u * kV2Waves) {
+                    // every lane takes part (a lane reads another's prefix); those
+                    // past the list repeat its last hit and store nothing
+                    const uint32_t j = c0 + lane;
+                    const uint32_t jc = j < nhit_1 ? j : nhit_1 - 1u;
+                    {
+                        const uint32_t at = hp[jc];
+                        const int row = (int)(__umul24(at, A->row_mul) >> A->row_sh), col = (int)(at - __umul24(row, W));
+                        const int bank = (int)(__umul24(col, A->bank_mul) >> kBankShift);
+                        const int i = (int)__umul24(row, nb) + bank;
+                        const int cb = col - (int)__umul24(bank, B);
+                        // (all words read at once: one LDS latency)
+                        const uint32_t *bwp = s_bits + __umul24(pp * RN + i, bw);
+                        uint32_t wd[kBitWords];
+#pragma unroll
+                        for (int w = 0; w < kBitWords; ++w) wd[w] = bwp[w];
+                        uint32_t rank = 0;
+#pragma unroll
+                        for (int w = 0; w < kBitWords; ++w) {
+                            const int k = cb - 32 * w;  // columns of word w left of the hit
+                            rank += __popc(wd[w] & (k >= 32 ? ~0u : (k > 0 ? (1u << k) - 1u : 0u)));
+                        }
+                        uint32_t first = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i, (int)pref[0]);
+#pragma unroll
+                        for (int k = 1; k < kCntRegs; ++k) {
+                            const uint32_t t = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i, (int)pref[k]);
+                            first = i >= 64 * k ? t : first;
+                        }
+                        const float q = hq[jc];
+                        if (j < nhit_1) pool[base + first + rank] = make_uint2(row_base + at, __float_as_uint(q));
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_s_setprio(0);
         PDC_PHASE(6);
     }
 #ifdef PDC_PHASE_TIMERS
@@ -1189,10 +1183,10 @@ __device__ __forceinline__ void frame_body(const V2Args &A, const int item)
 #undef PDC_PHASE
 }
 
-template <int NQ, int GMAX, int L, int V, bool KEEP, bool CMM, bool MG>
-__global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2(V2Args A)
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG>
+__global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2(V2Args)
 {
-    frame_body<NQ, GMAX, L, V, KEEP, CMM, MG>(A, block_item((int)blockIdx.x, (int)gridDim.x));
+    frame_body<L, Q, R, KEEP, CMM, MG>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
 }
 
 // Several detectors' batches in one launch: the work items of detector d are
@@ -1201,110 +1195,98 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
 // out), and each workgroup runs the body
 // compiled for its detector's lane layout and gain mode (median common mode,
 // Frames2 not kept: the variants v2_mix_variant lists).
-__global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2_mix(V2Mix M)
+__global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2_mix(V2Mix)
 {
+    const auto M = (const __attribute__((address_space(4))) V2Mix *)__builtin_amdgcn_kernarg_segment_ptr();
     // work items in launch order: consecutive workgroups go to different
     // chiplets, so each chiplet takes a share of every detector's items
     const int item = (int)blockIdx.x;
     int d = 0;
-    while (d + 1 < M.n && item >= M.first[d + 1]) ++d;
-    // fields are read from the argument memory where they are used (scalar
-    // loads, cached): copied into registers up front they would be spilled
-    const V2Args &A = M.a[d];
-    const int it = item - M.first[d];
-    switch (M.variant[d]) {
-    case 0: frame_body<2, 4, 16, 13, false, false, false>(A, it); break;
-    case 1: frame_body<2, 4, 16, 16, false, false, false>(A, it); break;
-    case 2: frame_body<1, 8, 8, 8, false, false, false>(A, it); break;
-    case 3: frame_body<1, 8, 8, 12, false, false, false>(A, it); break;
-    case 4: frame_body<1, 8, 8, 16, false, false, false>(A, it); break;
-    case 5: frame_body<2, 4, 16, 13, false, false, true>(A, it); break;
-    case 6: frame_body<2, 4, 16, 16, false, false, true>(A, it); break;
-    case 7: frame_body<1, 8, 8, 12, false, false, true>(A, it); break;
-    case 8: frame_body<1, 8, 8, 16, false, false, true>(A, it); break;
+    while (d + 1 < M->n && item >= M->first[d + 1]) ++d;
+    const V2ArgsK A = &M->a[d];
+    const int it = item - M->first[d];
+    switch (M->variant[d]) {
+    case 0: frame_body<4, 2, 0, false, 0, false>(A, it); break;
+    case 1: frame_body<4, 3, 0, false, 0, false>(A, it); break;
+    case 2: frame_body<8, 2, 0, false, 0, false>(A, it); break;
+    case 3: frame_body<8, 3, 1, false, 0, false>(A, it); break;
+    case 4: frame_body<16, 2, 0, false, 0, false>(A, it); break;
+    case 5: frame_body<4, 2, 0, false, 0, true>(A, it); break;
+    case 6: frame_body<4, 3, 0, false, 0, true>(A, it); break;
+    case 7: frame_body<8, 2, 0, false, 0, true>(A, it); break;
+    case 8: frame_body<8, 3, 1, false, 0, true>(A, it); break;
+    case 9: frame_body<16, 2, 0, false, 0, true>(A, it); break;
     default: break;
     }
 }
 
-template <int NQ, int GMAX, int L, int V, bool KEEP, bool CMM, bool MG = false>
+// Lane layouts (L lanes a bank-row, Q chunks of 8 columns and R single columns
+// a lane) by bank width.  Few lanes a bank-row pay the search's reductions,
+// control and sort once for more bank-rows (a wave holds 64 / L); the lane's
+// values, dark and 1/gain (3 V registers, with V = 4 Q + R) and the next
+// frame's words have to fit four waves per SIMD (128 registers).
+int v2_layout_of(int B)
+{
+    return B <= 64 ? 0 : (B <= 96 ? 1 : (B <= 128 ? 2 : (B <= 200 ? 3 : (B <= 256 ? 4 : -1))));
+}
+int v2_layout_bank_rows(int layout)
+{
+    return layout < 2 ? kV2Threads / 4 : (layout < 4 ? kV2Threads / 8 : kV2Threads / 16 * kV2Passes<16>);
+}
+
+size_t v2_layout_finish_bytes(int layout)
+{
+    return (size_t)kV2Threads * 4 * (layout < 2 ? kV2Finish<4> : (layout < 4 ? kV2Finish<8> : kV2Finish<16>));
+}
+
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG>
 static hipError_t launch_v2_k(const V2Args &a, uint32_t grid, size_t lds, hipStream_t s)
 {
-    auto k = frame_kernel_v2<NQ, GMAX, L, V, KEEP, CMM, MG>;
+    auto k = frame_kernel_v2<L, Q, R, KEEP, CMM, MG>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(grid), dim3(kV2Threads), lds, s, a);
     return hipGetLastError();
 }
 
-template <int NQ, int GMAX, int L, int V>
+template <int L, int Q, int R>
 static hipError_t launch_v2_t(const V2Args &a, uint32_t grid, size_t lds, bool keep, hipStream_t s)
 {
-    return keep ? launch_v2_k<NQ, GMAX, L, V, true, false>(a, grid, lds, s)
-                : launch_v2_k<NQ, GMAX, L, V, false, false>(a, grid, lds, s);
+    if (a.cm_mode < 0 || a.cm_mode > 2) return hipErrorInvalidValue;
+    switch (a.cm_mode * 4 + (keep ? 2 : 0) + (a.gain_mode ? 1 : 0)) {
+    case 0: return launch_v2_k<L, Q, R, false, 0, false>(a, grid, lds, s);
+    case 1: return launch_v2_k<L, Q, R, false, 0, true>(a, grid, lds, s);
+    case 2: return launch_v2_k<L, Q, R, true, 0, false>(a, grid, lds, s);
+    case 3: return launch_v2_k<L, Q, R, true, 0, true>(a, grid, lds, s);
+    case 4: return launch_v2_k<L, Q, R, false, 1, false>(a, grid, lds, s);
+    case 5: return launch_v2_k<L, Q, R, false, 1, true>(a, grid, lds, s);
+    case 6: return launch_v2_k<L, Q, R, true, 1, false>(a, grid, lds, s);
+    case 7: return launch_v2_k<L, Q, R, true, 1, true>(a, grid, lds, s);
+    case 8: return launch_v2_k<L, Q, R, false, 2, false>(a, grid, lds, s);
+    case 9: return launch_v2_k<L, Q, R, false, 2, true>(a, grid, lds, s);
+    case 10: return launch_v2_k<L, Q, R, true, 2, false>(a, grid, lds, s);
+    default: return launch_v2_k<L, Q, R, true, 2, true>(a, grid, lds, s);
+    }
 }
 
-// Lanes per bank-row in the median phase and values per lane (L, V): 16 lanes
-// for banks of more than 128 pixels, else 8 (strips hold at most 64 and 128
-// bank-rows, so L * bank-rows <= 1024), V = ceil(B / L) rounded up to a
-// compiled size.  Four to eight searches per wave and four waves per SIMD
-// hide the latency of the reductions.
-hipError_t launch_frame_kernel_v2(const V2Args &a, int nq, int gmax, uint32_t grid, size_t lds, bool keep,
-                                  hipStream_t s)
+hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bool keep, hipStream_t s)
 {
-    if (a.B < 1 || a.rmax * a.nb > 16 * gmax) return hipErrorInvalidValue;
-    if (a.gain_mode) {  // auto-ranging variants: one lane layout per strip shape
-        const bool cm = a.cm_mode != 0;
-        if (nq == 2 && gmax == 4 && a.B <= 256) {
-            if (cm) return keep ? launch_v2_k<2, 4, 16, 16, true, true, true>(a, grid, lds, s)
-                                : launch_v2_k<2, 4, 16, 16, false, true, true>(a, grid, lds, s);
-            if (a.B <= 16 * 13)
-                return keep ? launch_v2_k<2, 4, 16, 13, true, false, true>(a, grid, lds, s)
-                            : launch_v2_k<2, 4, 16, 13, false, false, true>(a, grid, lds, s);
-            return keep ? launch_v2_k<2, 4, 16, 16, true, false, true>(a, grid, lds, s)
-                        : launch_v2_k<2, 4, 16, 16, false, false, true>(a, grid, lds, s);
-        }
-        if (nq == 1 && gmax == 8 && a.B <= 128) {
-            if (cm) return keep ? launch_v2_k<1, 8, 8, 16, true, true, true>(a, grid, lds, s)
-                                : launch_v2_k<1, 8, 8, 16, false, true, true>(a, grid, lds, s);
-            if (a.B <= 8 * 12)
-                return keep ? launch_v2_k<1, 8, 8, 12, true, false, true>(a, grid, lds, s)
-                            : launch_v2_k<1, 8, 8, 12, false, false, true>(a, grid, lds, s);
-            return keep ? launch_v2_k<1, 8, 8, 16, true, false, true>(a, grid, lds, s)
-                        : launch_v2_k<1, 8, 8, 16, false, false, true>(a, grid, lds, s);
-        }
-        return hipErrorInvalidValue;
+    const int lay = v2_layout_of(a.B);
+    if (a.B < 1 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return hipErrorInvalidValue;
+    switch (lay) {
+    case 0: return launch_v2_t<4, 2, 0>(a, grid, lds, keep, s);
+    case 1: return launch_v2_t<4, 3, 0>(a, grid, lds, keep, s);
+    case 2: return launch_v2_t<8, 2, 0>(a, grid, lds, keep, s);
+    case 3: return launch_v2_t<8, 3, 1>(a, grid, lds, keep, s);
+    default: return launch_v2_t<16, 2, 0>(a, grid, lds, keep, s);
     }
-    if (a.cm_mode) {  // the thresholded-mean variant: no median search
-        if (nq == 2 && gmax == 4 && a.B <= 256)
-            return keep ? launch_v2_k<2, 4, 16, 16, true, true>(a, grid, lds, s)
-                        : launch_v2_k<2, 4, 16, 16, false, true>(a, grid, lds, s);
-        if (nq == 1 && gmax == 8 && a.B <= 128)
-            return keep ? launch_v2_k<1, 8, 8, 16, true, true>(a, grid, lds, s)
-                        : launch_v2_k<1, 8, 8, 16, false, true>(a, grid, lds, s);
-        return hipErrorInvalidValue;
-    }
-    if (nq == 2 && gmax == 4 && a.B <= 256) {
-        if (a.B <= 16 * 13) return launch_v2_t<2, 4, 16, 13>(a, grid, lds, keep, s);
-        return launch_v2_t<2, 4, 16, 16>(a, grid, lds, keep, s);
-    }
-    if (nq == 1 && gmax == 8 && a.B <= 128) {
-        if (a.B <= 8 * 8) return launch_v2_t<1, 8, 8, 8>(a, grid, lds, keep, s);
-        if (a.B <= 8 * 12) return launch_v2_t<1, 8, 8, 12>(a, grid, lds, keep, s);
-        return launch_v2_t<1, 8, 8, 16>(a, grid, lds, keep, s);
-    }
-    return hipErrorInvalidValue;
 }
 
-int v2_mix_variant(const V2Args &a, int nq, int gmax, bool keep)
+int v2_mix_variant(const V2Args &a, bool keep)
 {
-    if (keep || a.cm_mode || a.meds || a.B < 1 || a.rmax * a.nb > 16 * gmax) return -1;
-    const int mg = a.gain_mode ? 5 : 0;
-    if (nq == 2 && gmax == 4 && a.B <= 256) return a.B <= 16 * 13 ? mg : mg + 1;
-    if (nq == 1 && gmax == 8 && a.B <= 128) {
-        if (a.B <= 8 * 8 && !a.gain_mode) return 2;
-        return a.B <= 8 * 12 ? (a.gain_mode ? 7 : 3) : (a.gain_mode ? 8 : 4);
-    }
-    return -1;
+    const int lay = v2_layout_of(a.B);
+    if (keep || a.cm_mode || a.meds || a.B < 1 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return -1;
+    return lay + (a.gain_mode ? 5 : 0);
 }
 
 size_t frame_kernel_v2_mix_static_lds()

@@ -12,8 +12,10 @@ constexpr uint64_t kNoBase = ~0ull;
 
 // Waves per workgroup of the persistent kernel; 16 / kV2Waves workgroups
 // share a compute unit (its LDS split between them, four waves per SIMD).
+// Eight: a strip of 30 own CSPAD rows fills eight waves' bank-rows, and one
+// workgroup's waits at its barriers are the other's time.
 #ifndef PDC_V2_WAVES
-#define PDC_V2_WAVES 16
+#define PDC_V2_WAVES 8
 #endif
 constexpr int kV2Waves = PDC_V2_WAVES;
 constexpr int kV2Threads = kV2Waves * 64;
@@ -108,11 +110,19 @@ struct V2Args {
     int32_t gain_mode;
     uint32_t *invalid;
     float *meds;                  // as in FrameKernelArgs (median mode)
-    int32_t med_row_step;         // single-gain median kernels with 16-lane groups: 4 when one
-                                  // wave's four groups take every fourth row, else 0
+    int32_t hit_cap;              // hits per strip-frame held in LDS
+    uint32_t row_mul, row_sh;     // at / W = (at * row_mul) >> row_sh for positions of a strip
+    uint32_t bank_mul;            // col / B = (col * bank_mul) >> kBankShift for col < 2048
 };
 
-size_t frame_kernel_v2_lds_bytes(int rmax, int W, int nb, int seed_cap);
+constexpr int kBankShift = 20;
+// Compiled lane layout for banks of B pixels (-1: none), the bank-rows a
+// workgroup holds with it and the bytes of its medians' finish scratch, which
+// lies in a hit list.
+int v2_layout_of(int B);
+int v2_layout_bank_rows(int layout);
+size_t v2_layout_finish_bytes(int layout);
+size_t frame_kernel_v2_lds_bytes(int rmax, int W, int B, int nb, int seed_cap, int hit_cap);
 // Several detectors' batches in one launch of the persistent kernel: the
 // work items (strip, frame group) of detector d are [first[d], first[d + 1]).
 constexpr int kMixMax = 8;
@@ -126,14 +136,13 @@ static_assert(sizeof(V2Mix) <= 4096, "V2Mix is passed as a kernel argument");
 // The compiled body of the one launch for a batch, or -1 when it has none
 // (Frames2 or common-mode values kept, thresholded mean): such batches take
 // launches of their own.
-int v2_mix_variant(const V2Args &a, int nq, int gmax, bool keep);
+int v2_mix_variant(const V2Args &a, bool keep);
 // Dynamic LDS lds: at least the largest v2 LDS of the detectors.
 hipError_t launch_frame_kernel_v2_mix(const V2Mix &m, size_t lds, hipStream_t s);
 // Static LDS of that kernel (every body's own variables), SIZE_MAX if unknown.
 size_t frame_kernel_v2_mix_static_lds();
 // a.cm_mode != 0 selects the thresholded-mean variant (no median search)
-hipError_t launch_frame_kernel_v2(const V2Args &a, int nq, int gmax, uint32_t grid, size_t lds, bool keep,
-                                  hipStream_t s);
+hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bool keep, hipStream_t s);
 
 // Thresholded-mean common mode (Fig. c), computed ahead of the frame kernels:
 // cm[f][region][s] for stages s < stages, zeros after.  A region's sum is the

@@ -58,7 +58,7 @@ struct Detector {
     size_t lds_bytes = 0;
     // persistent kernel (v2): resident calibration per strip
     bool v2_ok = false;
-    int nq = 0, gmax = 0, n_strips = 0, rmax = 0, seed_cap = 0;
+    int n_strips = 0, rmax = 0, max_rows = 0, seed_cap = 0, hit_cap = 0;  // max_rows: loaded rows a workgroup holds
     int n_cu = 0;                         // compute units of the device (frame-group choice)
     int fg_mult = 1;                      // frame groups x this (pdc_autotune)
     int strip_cap = 0;                    // own rows per strip at most this (0: as many as fit; pdc_autotune_strips)
@@ -372,10 +372,26 @@ bool plan_v2(pdc_ctx *ctx, Detector &d)
     if (!g.gain_mode && (g.cols % 4))
         return false;
     const int nb = g.cols / g.bank_cols;
-    d.nq = g.bank_cols > 128 ? 2 : 1;
-    d.gmax = d.nq == 2 ? 4 : 8;
-    const int max_bank_rows = kV2Waves * d.gmax;  // a bank-row group per wave and slot
-    const int rmax_lim = max_bank_rows / nb;
+    const int layout = v2_layout_of(g.bank_cols);
+    const int max_bank_rows = v2_layout_bank_rows(layout);
+    int rmax_lim = max_bank_rows / nb;
+    // room in LDS for seeds on a twelfth of the strip's pixels at least (1024-
+    // column detectors: 15 rows rather than 16)
+    const size_t lds_wg = (size_t)ctx->max_lds / kV2GroupsPerCu;
+#ifdef PDC_PHASE_TIMERS
+    const size_t static_lds = 2048;  // the tracing build's per-wave counters
+#else
+    const size_t static_lds = 512;
+#endif
+    const size_t lds_cap = lds_wg > static_lds ? lds_wg - static_lds : 0;
+    const size_t min_hits = (v2_layout_finish_bytes(layout) + 5) / 6;
+    auto lds_base = [&](int rows) {  // 64: rounding of the lists
+        return frame_kernel_v2_lds_bytes(rows, g.cols, g.bank_cols, nb, 0, 0) + 64;
+    };
+    while (rmax_lim >= 3 &&
+           lds_base(rmax_lim) + 16 * std::max<size_t>(min_hits, (size_t)rmax_lim * g.cols / 24) > lds_cap)
+        --rmax_lim;
+    d.max_rows = rmax_lim;
     if (rmax_lim < 3) return false;
     const int own_max = d.strip_cap > 0 ? std::min(rmax_lim - 2, d.strip_cap) : rmax_lim - 2;
     // Strips of at most own_max own rows over the frame's rows counted across
@@ -415,21 +431,18 @@ bool plan_v2(pdc_ctx *ctx, Detector &d)
     // local maxima of a strip's own rows: at most every other row and column
     // of each tile part (two parts when the strip crosses a tile edge)
     d.v2_max_unit_hits = (uint32_t)((own_rows_max + 3) / 2) * (uint32_t)((g.cols + 1) / 2);
-    // seed lists: as large as the workgroup's LDS allows (the kernel's
-    // registers admit one workgroup per compute unit anyway), at least 1024
-    // entries; 512 bytes stay free for the kernel's static LDS (the one-launch
-    // mixed kernel holds every body's own variables)
-    const size_t lds_wg = (size_t)ctx->max_lds / kV2GroupsPerCu;
-#ifdef PDC_PHASE_TIMERS
-    const size_t static_lds = 2048;  // the tracing build's per-wave counters
-#else
-    const size_t static_lds = 512;
-#endif
-    const size_t lds_cap = lds_wg > static_lds ? lds_wg - static_lds : 0;
-    size_t base = frame_kernel_v2_lds_bytes(rmax, g.cols, nb, 0);
-    if (base + 4 * 4 * 1024 > lds_cap) return false;
-    d.seed_cap = (int)std::min<size_t>((lds_cap - base) / 16, 16384);
-    d.v2_lds = frame_kernel_v2_lds_bytes(rmax, g.cols, nb, d.seed_cap);
+    // seed list (2 bytes an entry) and two hit lists half as long (6 bytes):
+    // as large as the workgroup's LDS allows (the kernel's registers admit one
+    // workgroup per compute unit anyway), a hit list at least the medians'
+    // finish scratch; 512 bytes stay free for the kernel's static LDS (the
+    // one-launch mixed kernel holds every body's own variables)
+    const size_t base = lds_base(rmax);
+    if (base + 16 * min_hits > lds_cap) return false;
+    // (seeds on more than two fifths of a strip's pixels, flood frames, are left
+    // to the general kernel whatever the LDS holds)
+    d.hit_cap = (int)std::max(min_hits, std::min<size_t>((lds_cap - base) / 16, (size_t)rmax * g.cols / 5));
+    d.seed_cap = 2 * d.hit_cap;
+    d.v2_lds = frame_kernel_v2_lds_bytes(rmax, g.cols, g.bank_cols, nb, d.seed_cap, d.hit_cap);
     // the general kernel sized for one of these strips (own rows + halo), to
     // redo the units whose seed lists overflow
     d.fb_ok = false;
@@ -657,34 +670,6 @@ pdc_status enqueue_pre(pdc_ctx *ctx, Batch &bt)
     return PDC_OK;
 }
 
-// Rows between the bank-rows that one wave's four 16-lane median groups read:
-// 4 or 0 (consecutive bank-rows).  Each group reads 16 consecutive LDS words
-// per value slot from its bank-row's start; every fourth row is taken when it
-// spreads the four windows more evenly over the 64 LDS banks (W = 388: starts
-// 16 banks apart, no conflict, against four-way conflicts for consecutive
-// bank-rows).
-static int median_row_step(int W, int B, int nb)
-{
-    auto worst = [](const int(&off)[4]) {
-        int cnt[64] = {}, mx = 0;
-        for (int g = 0; g < 4; ++g)
-            for (int k = 0; k < 16; ++k) mx = std::max(mx, ++cnt[(off[g] + k) & 63]);
-        return mx;
-    };
-    int off[4];
-    for (int g = 0; g < 4; ++g) off[g] = (g / nb) * W + (g % nb) * B;
-    int best = 0, best_w = worst(off);
-    for (int step : {4}) {
-        for (int g = 0; g < 4; ++g) off[g] = g * step * W;
-        const int w = worst(off);
-        if (w < best_w) {
-            best = step;
-            best_w = w;
-        }
-    }
-    return best;
-}
-
 // Arguments of the persistent kernel for a batch.
 void fill_v2_args(const Detector &d, const Batch &bt, V2Args &a)
 {
@@ -726,7 +711,14 @@ void fill_v2_args(const Detector &d, const Batch &bt, V2Args &a)
     a.cm_guard = d.cm_guard;
     a.sum_lo = d.sum_lo;
     a.sum_hi = d.sum_hi;
-    a.med_row_step = d.nq == 2 ? median_row_step(a.W, a.B, a.nb) : 0;
+    a.hit_cap = d.hit_cap;
+    // n / W = (n * ceil(2^s / W)) >> s for n W <= 2^s, and n * ceil(2^s / W) <
+    // 2^32 for the n <= 40960 positions that fit the LDS; likewise col / B
+    const uint64_t positions = (uint64_t)d.rmax * a.W;
+    a.row_sh = 1;
+    while (((uint64_t)1 << a.row_sh) < positions * a.W) ++a.row_sh;
+    a.row_mul = (uint32_t)((((uint64_t)1 << a.row_sh) + a.W - 1) / a.W);
+    a.bank_mul = (uint32_t)(((1u << kBankShift) + a.B - 1) / a.B);
     a.gain_mode = d.g.gain_mode;
     a.invalid = b->invalid;
     a.meds = bt.meds && !d.p.cm_mode ? b->meds : nullptr;
@@ -748,7 +740,7 @@ pdc_status enqueue(pdc_ctx *ctx, Batch &bt)
     if (bt.n_units > 0 && bt.path == 2) {
         V2Args a;
         fill_v2_args(d, bt, a);
-        HIP_TRY(ctx, launch_frame_kernel_v2(a, d.nq, d.gmax, batch_grid(d, bt), d.v2_lds, bt.keep, s));
+        HIP_TRY(ctx, launch_frame_kernel_v2(a, batch_grid(d, bt), d.v2_lds, bt.keep, s));
     } else if (bt.n_units > 0) {
         FrameKernelArgs a{};
         fill_v1_args(d, bt, a);
@@ -776,7 +768,7 @@ bool mix_one_launch(pdc_ctx *ctx, const std::vector<int32_t> &dets)
         a.rmax = d.rmax;
         a.gain_mode = d.g.gain_mode;
         a.cm_mode = d.p.cm_mode == PDC_CM_MEDIAN ? 0 : 1;
-        if ((d.p.flags & PDC_KEEP_MEDIANS) || v2_mix_variant(a, d.nq, d.gmax, (d.p.flags & PDC_KEEP_CORRECTED) != 0) < 0)
+        if ((d.p.flags & PDC_KEEP_MEDIANS) || v2_mix_variant(a, (d.p.flags & PDC_KEEP_CORRECTED) != 0) < 0)
             return false;
         lds = std::max(lds, d.v2_lds);
     }
@@ -841,7 +833,7 @@ pdc_status enqueue_mixed(pdc_ctx *ctx, std::vector<Batch *> &bts, hipStream_t s,
         const Batch &bt = *bts[i];
         const Detector &d = ctx->dets[bt.det];
         fill_v2_args(d, bt, m.a[i]);
-        m.variant[i] = v2_mix_variant(m.a[i], d.nq, d.gmax, bt.keep);
+        m.variant[i] = v2_mix_variant(m.a[i], bt.keep);
         m.first[i] = first;
         first += (int)batch_grid(d, bt);
         lds = std::max(lds, d.v2_lds);
@@ -881,8 +873,8 @@ pdc_status enqueue_partial(pdc_ctx *ctx, Batch &bt, uint64_t n_list)
 
 // Frame groups of a persistent launch: each workgroup takes one strip for a
 // contiguous range of frames, one workgroup per compute unit at a time, and
-// spends two extra pipeline iterations draining.  The count minimises
-// rounds x (frames per group + 2), the iterations a compute unit runs: large
+// spends an extra pipeline iteration draining.  The count minimises
+// rounds x (frames per group + 1), the iterations a compute unit runs: large
 // batches get enough groups to fill whole rounds of the chip (CSPAD's 198
 // strips alone would leave 58 of 256 units idle), small ones stay in one round.
 int frame_groups(int n_cu, int n_strips, uint64_t n_frames, int mult)
@@ -893,7 +885,7 @@ int frame_groups(int n_cu, int n_strips, uint64_t n_frames, int mult)
     for (int g = 1; g <= max_fg; ++g) {
         const uint64_t wgs = (uint64_t)g * n_strips;
         const uint64_t rounds = (wgs + n_cu - 1) / n_cu;
-        const uint64_t cost = rounds * ((n_frames + g - 1) / g + 2);
+        const uint64_t cost = rounds * ((n_frames + g - 1) / g + 1);
         if (cost < best_cost) {
             best_cost = cost;
             best = g;
@@ -2396,7 +2388,7 @@ pdc_status pdc_autotune_strips(pdc_ctx *ctx, int32_t det, const uint16_t *frames
     // own rows per strip: the most the lane layout holds, then 4 and 8 fewer
     d.strip_cap = 0;
     if (!plan_v2(ctx, d)) return fail(ctx, PDC_EDEVICE, "re-plan failed");
-    const int full = kV2Waves * d.gmax / (d.g.cols / d.g.bank_cols) - 2;  // as plan_v2 allows
+    const int full = d.max_rows - 2;  // as plan_v2 allows
     int caps[3] = {full, full - 4, full - 8};
     int n_caps = 1;
     while (n_caps < 3 && caps[n_caps] >= 4) ++n_caps;
