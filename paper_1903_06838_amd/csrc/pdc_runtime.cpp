@@ -1823,13 +1823,20 @@ pdc_status capture(pdc_ctx *ctx, uint64_t batch, float *patches, uint16_t *input
     hipStream_t cs = ctx->copy_stream;
     HIP_TRY(ctx, hipStreamWaitEvent(cs, b->ev_end, 0));
     const uint64_t n = std::min<uint64_t>(b->host_state->total, capacity);
-    if (bt->keep) {
-        HIP_TRY(ctx, launch_capture_patches(b->corrected, b->hits, b->frame_offset, bt->n_frames, n, d.g.n_tiles,
-                                            d.g.rows, d.g.cols, patches, inputs, inv_adu, cs));
-    } else {
-        HIP_TRY(ctx, launch_patches_from_frames(patch_src(d, *bt), b->hits, b->frame_offset, bt->n_frames, n, patches,
-                                                inputs, inv_adu, cs));
-    }
+    CaptureArgs c{};
+    c.src = patch_src(d, *bt);
+    c.corrected = bt->keep ? b->corrected : nullptr;
+    c.hits = b->hits;
+    c.unit_count = b->unit_count;
+    c.unit_local = b->unit_local;
+    c.frame_offset = b->frame_offset;
+    c.n_frames = bt->n_frames;
+    c.upf = (uint32_t)bt->upf;
+    c.n = n;
+    c.patches = patches;
+    c.inputs = inputs;
+    c.inv_adu = inv_adu;
+    HIP_TRY(ctx, launch_capture(c, (uint32_t)ctx->n_cu, cs));
     HIP_TRY(ctx, hipStreamSynchronize(cs));
     if (n_out) *n_out = n;
     return PDC_OK;

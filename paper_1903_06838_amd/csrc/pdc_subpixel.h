@@ -49,11 +49,6 @@ hipError_t launch_mlp_grad(const float *patches, const float *target, uint64_t n
 hipError_t launch_mlp_train(const float *patches, const float *target, uint64_t n, float inv_adu, float *theta,
                             float *m, float *v, uint16_t *packed, float *grad, float *slots, uint32_t max_grid,
                             float lr, int64_t step, hipStream_t s);
-// patches float32 [n][25], or, when inputs is not NULL, the network's inputs
-// uint16 [n][kMlpInWords] (bf16 of each value times inv_adu, zero padding)
-hipError_t launch_capture_patches(const float *corrected, const uint2 *hits,
-                                  const unsigned long long *frame_offset, uint64_t n_frames, uint64_t n, int T,
-                                  int H, int W, float *patches, uint16_t *inputs, float inv_adu, hipStream_t s);
 // Patches rebuilt from the frames: Frames2 of each window pixel from its raw
 // word, the calibration and the frame's kept common-mode values (meds: bank
 // medians [n_frames][T*H*nb]; or, with meds null, the thresholded mean's
@@ -67,9 +62,25 @@ struct PatchSrc {
     uint32_t cm_regions;
     int32_t cm_tile;
 };
-hipError_t launch_patches_from_frames(const PatchSrc &a, const uint2 *hits, const unsigned long long *frame_offset,
-                                      uint64_t n_frames, uint64_t n, float *patches, uint16_t *inputs, float inv_adu,
-                                      hipStream_t s);
+// Patches (float32 [n][25]) or, when inputs is not NULL, the network's inputs
+// (uint16 [n][kMlpInWords]: bf16 of each value times inv_adu, zero padding) of
+// the first n hits of a batch, whose units' runs are given as the scans left
+// them; from Frames2 (corrected != NULL) or formed again from the frames (src).
+struct CaptureArgs {
+    PatchSrc src;
+    const float *corrected;
+    const uint2 *hits;
+    const uint32_t *unit_count, *unit_local;   // [n_frames][upf]
+    const unsigned long long *frame_offset;    // [n_frames + 1]
+    uint64_t n_frames;
+    uint32_t upf;
+    uint64_t frames_per_item;                  // set by the launch
+    uint64_t n;
+    float *patches;
+    uint16_t *inputs;
+    float inv_adu;
+};
+hipError_t launch_capture(CaptureArgs a, uint32_t n_cu, hipStream_t s);
 // Centroid (+ eta) positions of the first n hits of a batch, from Frames2
 // (corrected != NULL) or formed again from the frames (a); only_bad: replace
 // only the positions in pos that are not finite or outside [-1, 1].

@@ -894,33 +894,6 @@ hipError_t launch_mlp_train(const float *patches, const float *target, uint64_t 
     return hipGetLastError();
 }
 
-// 5x5 neighbourhood of each hit in the corrected frames (zero outside the
-// tile).  hits[i] = {pixel, charge bits} of the raster-order list; its frame
-// is the largest f with frame_offset[f] <= i.
-// A captured patch goes out as 25 float32 values (patches[i][25]) or as the
-// network's input (inputs != nullptr): bf16(fl(v * inv_adu)) of each value,
-// then 7 zero words, 64 bytes per hit (inputs[i][32]).
-__device__ __forceinline__ void store_patch(const float (&v)[25], uint64_t i, float *patches, uint16_t *inputs,
-                                            float inv_adu)
-{
-    if (inputs) {
-        u32x4 *dst = reinterpret_cast<u32x4 *>(inputs + i * kMlpInWords);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            u32x4 w;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int e = 8 * q + 2 * j;
-                w[j] = pk_bf16(e < 25 ? v[e] * inv_adu : 0.0f, e + 1 < 25 ? v[e + 1] * inv_adu : 0.0f);
-            }
-            dst[q] = w;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 25; ++e) patches[i * 25 + e] = v[e];
-    }
-}
-
 // Frame of hit i: the last frame whose first hit is at most i.
 __device__ __forceinline__ uint64_t hit_frame(const unsigned long long *frame_offset, uint64_t n_frames, uint64_t i)
 {
@@ -931,39 +904,6 @@ __device__ __forceinline__ uint64_t hit_frame(const unsigned long long *frame_of
         else hi = mid;
     }
     return lo;
-}
-
-__global__ void capture_patches_kernel(const float *corrected, const uint2 *hits,
-                                       const unsigned long long *frame_offset, uint64_t n_frames, uint64_t n, int T,
-                                       int H, int W, float *patches, uint16_t *inputs, float inv_adu)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t lo = hit_frame(frame_offset, n_frames, i);
-    const uint32_t p = hits[i].x;
-    const int c = (int)(p % (uint32_t)W);
-    const int rt = (int)(p / (uint32_t)W);
-    const int t = rt / H, r = rt - t * H;
-    const float *fr = corrected + (lo * (uint64_t)T + (uint64_t)t) * (uint64_t)H * W;
-    float v[25];
-#pragma unroll
-    for (int dr = -2; dr <= 2; ++dr)
-#pragma unroll
-        for (int dc = -2; dc <= 2; ++dc) {
-            const int rr = r + dr, cc = c + dc;
-            v[(dr + 2) * 5 + dc + 2] = (rr >= 0 && rr < H && cc >= 0 && cc < W) ? fr[(uint64_t)rr * W + cc] : 0.0f;
-        }
-    store_patch(v, i, patches, inputs, inv_adu);
-}
-
-hipError_t launch_capture_patches(const float *corrected, const uint2 *hits, const unsigned long long *frame_offset,
-                                  uint64_t n_frames, uint64_t n, int T, int H, int W, float *patches,
-                                  uint16_t *inputs, float inv_adu, hipStream_t s)
-{
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(capture_patches_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, corrected, hits,
-                       frame_offset, n_frames, n, T, H, W, patches, inputs, inv_adu);
-    return hipGetLastError();
 }
 
 // Frames2 of pixel (rr, cc) of tile t of frame lo, formed again from its raw
@@ -988,29 +928,161 @@ __device__ __forceinline__ float frames2_at(const PatchSrc &a, uint64_t lo, int 
     return bad ? 0.0f : __fsub_rn(__fsub_rn(__fsub_rn(u, cv[0]), cv[1]), cv[2]);
 }
 
-// The same patches without Frames2: each window pixel's Frames2 value formed
-// again (frames2_at).
-__global__ void patches_from_frames_kernel(PatchSrc a, const uint2 *hits, const unsigned long long *frame_offset,
-                                           uint64_t n_frames, uint64_t n, float *patches, uint16_t *inputs,
-                                           float inv_adu)
+// The 5x5 neighbourhood of each hit's Frames2 values (zero outside the tile),
+// in hit-list order, as 25 float32 values (patches[i][25]) or as the network's
+// input (inputs != nullptr): bf16(fl(v * inv_adu)) of each value, then 7 zero
+// words, 64 bytes a hit (inputs[i][32]).  FRAMES2: the values are copied from
+// the kept Frames2 (a.corrected); else each is formed again from its raw word,
+// the calibration and the kept common-mode values (the operations of
+// frames2_at).
+//
+// A wave takes the runs of one strip in consecutive frames (hits of a unit are
+// consecutive in the list), 12 hits at a time, a lane per window row: 5
+// neighbouring columns are one or two loads of each plane, where a lane per
+// hit made 25 scattered ones.  The patches go out through LDS as contiguous
+// words.  Work items are ordered by strip and dealt to the chiplets in
+// contiguous ranges, so a strip's dark and 1/gain stay in one L2 for all its
+// frames; hits taken in list order read both planes anew from beyond the L2
+// for every frame.  For the 0.72 million hits of 64 CSPAD frames at occupancy
+// 0.005 (network inputs from kept medians): 100 us, 734 us by a lane per hit.
+constexpr int kPatchHits = 12;   // hits of a wave at once (5 lanes each)
+constexpr int kPatchWaves = 4;   // waves of a workgroup
+
+struct __attribute__((packed, aligned(2))) Raw5 {
+    uint16_t w[5];
+};
+struct __attribute__((packed, aligned(4))) Float5 {
+    float v[5];
+};
+
+template <bool FRAMES2>
+__global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t lo = hit_frame(frame_offset, n_frames, i);
-    const int H = a.H, W = a.W;
-    const uint32_t p = hits[i].x;
-    const int c = (int)(p % (uint32_t)W);
-    const int rt = (int)(p / (uint32_t)W);
-    const int t = rt / H, r = rt - t * H;
-    float out[25];
+    __shared__ __align__(16) float s_p[kPatchWaves][kPatchHits * 25];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // item (strip, frame group) of the wave: blocks are dealt to the 8 chiplets
+    // round-robin, and the chiplets take contiguous ranges of items
+    const uint32_t nblk = gridDim.x, x = blockIdx.x & 7u;
+    uint32_t before = 0;
+    for (uint32_t y = 0; y < x; ++y) before += (nblk - y + 7u) >> 3;
+    const uint64_t item = (uint64_t)(before + (blockIdx.x >> 3)) * kPatchWaves + wv;
+    const uint64_t ngrp = (a.n_frames + a.frames_per_item - 1) / a.frames_per_item;
+    if (item >= ngrp * a.upf) return;
+    const uint32_t strip = (uint32_t)(item / ngrp);
+    const uint64_t f0 = (item - strip * ngrp) * a.frames_per_item;
+    const uint64_t f1 = f0 + a.frames_per_item < a.n_frames ? f0 + a.frames_per_item : a.n_frames;
+    const int H = a.src.H, W = a.src.W, B = a.src.B;
+    const uint64_t npix = (uint64_t)a.src.T * H * W;
+    const int hl = lane / 5 < kPatchHits ? lane / 5 : kPatchHits - 1, wr = lane - 5 * (lane / 5);  // hit, window row
+    const bool on = lane < 5 * kPatchHits;
+    float *sp = s_p[wv];
+    for (uint64_t f = f0; f < f1; ++f) {
+        const uint64_t unit = f * a.upf + strip;
+        const uint32_t c_all = a.unit_count[unit];
+        const uint64_t i0 = a.frame_offset[f] + a.unit_local[unit];
+        const uint32_t cnt = i0 >= a.n ? 0u : (uint32_t)(a.n - i0 < c_all ? a.n - i0 : c_all);
+        for (uint32_t j0 = 0; j0 < cnt; j0 += kPatchHits) {
+            const uint32_t nh = cnt - j0 < (uint32_t)kPatchHits ? cnt - j0 : (uint32_t)kPatchHits;
+            float v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            if (on && (uint32_t)hl < nh) {
+                const uint32_t p = a.hits[i0 + j0 + hl].x;
+                const uint32_t rt = p / (uint32_t)W;
+                const int c = (int)(p - rt * (uint32_t)W) - 2;  // first column of the window
+                const int t = (int)(rt / (uint32_t)H), r = (int)rt - t * H + wr - 2;
+                const bool row_in = r >= 0 && r < H;
+                const uint64_t q = ((uint64_t)t * H + r) * (uint64_t)W + c;  // in the frame (used when inside)
+                const bool whole = c >= 0 && c + 4 < W;
+                if constexpr (FRAMES2) {
+                    const float *src = a.corrected + f * npix + q;
+                    if (row_in && whole) {
+                        const Float5 w = *reinterpret_cast<const Float5 *>(src);
 #pragma unroll
-    for (int dr = -2; dr <= 2; ++dr)
+                        for (int e = 0; e < 5; ++e) v[e] = w.v[e];
+                    } else if (row_in) {
 #pragma unroll
-        for (int dc = -2; dc <= 2; ++dc) {
-            const int rr = r + dr, cc = c + dc;
-            out[(dr + 2) * 5 + dc + 2] = (rr >= 0 && rr < H && cc >= 0 && cc < W) ? frames2_at(a, lo, t, rr, cc) : 0.0f;
+                        for (int e = 0; e < 5; ++e)
+                            if (c + e >= 0 && c + e < W) v[e] = src[e];
+                    }
+                } else if (row_in && whole && !a.src.gain_mode && B >= 4) {
+                    const Raw5 w = *reinterpret_cast<const Raw5 *>(a.src.frames + f * npix + q);
+                    const Float5 pd = *reinterpret_cast<const Float5 *>(a.src.ped + q);
+                    const Float5 kk = *reinterpret_cast<const Float5 *>(a.src.k + q);
+                    // the window's columns lie in at most two banks (B >= 4)
+                    const uint32_t grow = (uint32_t)(t * H + r);
+                    const int b0 = c / B, b4 = (c + 4) / B, edge = b4 * B - c;  // first column in bank b4
+                    float lo[3] = {0.0f, 0.0f, 0.0f}, hi[3] = {0.0f, 0.0f, 0.0f};
+                    const bool meds = a.src.meds != nullptr;
+                    if (meds) {
+                        const float *m = a.src.meds + (f * (uint64_t)a.src.T * H + grow) * (uint64_t)a.src.nb;
+                        lo[0] = m[b0];
+                        hi[0] = m[b4];
+                    } else {
+                        const uint64_t fr = f * a.src.cm_regions;
+                        const uint32_t r0 = a.src.cm_tile ? (uint32_t)t : grow * (uint32_t)a.src.nb + (uint32_t)b0;
+                        const uint32_t r4 = a.src.cm_tile ? (uint32_t)t : grow * (uint32_t)a.src.nb + (uint32_t)b4;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) {
+                            lo[k] = a.src.cm[(fr + r0) * 3 + k];
+                            hi[k] = a.src.cm[(fr + r4) * 3 + k];
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 5; ++e) {
+                        const bool up = b4 != b0 && e >= edge;
+                        float y = __fsub_rn(dark_gain(w.w[e], pd.v[e], kk.v[e]), up ? hi[0] : lo[0]);
+                        if (!meds) y = __fsub_rn(__fsub_rn(y, up ? hi[1] : lo[1]), up ? hi[2] : lo[2]);
+                        v[e] = y;
+                    }
+                } else if (row_in) {
+#pragma unroll
+                    for (int e = 0; e < 5; ++e)
+                        if (c + e >= 0 && c + e < W) v[e] = frames2_at(a.src, f, t, r, c + e);
+                }
+            }
+            if (on) {
+#pragma unroll
+                for (int e = 0; e < 5; ++e) sp[hl * 25 + wr * 5 + e] = v[e];
+            }
+            wave_lds_wait();
+            const uint64_t out0 = i0 + j0;
+            if (a.inputs) {
+                // lane 4 h + q: words 8 q .. 8 q + 7 of hit h
+                const int h = lane >> 2, q = lane & 3;
+                if ((uint32_t)h < nh) {
+                    u32x4 w;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int e = 8 * q + 2 * j;
+                        w[j] = pk_bf16(e < 25 ? sp[h * 25 + e] * a.inv_adu : 0.0f,
+                                       e + 1 < 25 ? sp[h * 25 + e + 1] * a.inv_adu : 0.0f);
+                    }
+                    reinterpret_cast<u32x4 *>(a.inputs + (out0 + h) * kMlpInWords)[q] = w;
+                }
+            } else {
+                for (uint32_t e = lane; e < nh * 25u; e += 64u) a.patches[out0 * 25 + e] = sp[e];
+            }
+            wave_lds_wait();
         }
-    store_patch(out, i, patches, inputs, inv_adu);
+    }
+}
+
+// Frames of an item: enough items for about 16 waves a compute unit, and a
+// Frames of an item: enough items for 32 waves a compute unit (8: 137 us, 16:
+// 114, 32: 100 at the size above), and where there are more a strip's frames
+// taken one after another.
+hipError_t launch_capture(CaptureArgs a, uint32_t n_cu, hipStream_t s)
+{
+    if (a.n == 0 || a.n_frames == 0 || a.upf == 0) return hipSuccess;
+    const uint64_t units = a.n_frames * (uint64_t)a.upf, want = 32ull * (n_cu ? n_cu : 256u);
+    a.frames_per_item = units / want > 1 ? units / want : 1;
+    if (a.frames_per_item > a.n_frames) a.frames_per_item = a.n_frames;
+    const uint64_t items = (a.n_frames + a.frames_per_item - 1) / a.frames_per_item * a.upf;
+    const uint64_t blocks = (items + kPatchWaves - 1) / kPatchWaves;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const auto k = a.corrected ? capture_kernel<true> : capture_kernel<false>;
+    hipLaunchKernelGGL(k, dim3((uint32_t)blocks), dim3(64 * kPatchWaves), 0, s, a);
+    return hipGetLastError();
 }
 
 // Classical positions straight from a batch: the masked 3x3 centroid of each
@@ -1061,16 +1133,6 @@ hipError_t launch_centroids(const PatchSrc &a, const float *corrected, const uin
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(centroids_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, a, corrected, hits,
                        frame_offset, n_frames, n, t_nb, eta, nbins, only_bad, pos);
-    return hipGetLastError();
-}
-
-hipError_t launch_patches_from_frames(const PatchSrc &a, const uint2 *hits, const unsigned long long *frame_offset,
-                                      uint64_t n_frames, uint64_t n, float *patches, uint16_t *inputs, float inv_adu,
-                                      hipStream_t s)
-{
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(patches_from_frames_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, a, hits,
-                       frame_offset, n_frames, n, patches, inputs, inv_adu);
     return hipGetLastError();
 }
 
