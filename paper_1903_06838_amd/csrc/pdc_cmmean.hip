@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kCmThreads) void cm_bank_kernel(CmArgs a)
 // it with K-bit limbs.
 template <int F>
 __device__ __forceinline__ bool tile_window(const CmArgs &a, int s, uint64_t f0, uint32_t t, int nf, int K,
-                                            float (&c0)[F], float (&c1)[F], int &lo)
+                                            float (&c0)[F], float (&c1)[F], int &lo, int &hi)
 {
     int l = a.sum_lo, h = a.sum_hi;
 #pragma unroll
@@ -135,6 +135,7 @@ __device__ __forceinline__ bool tile_window(const CmArgs &a, int s, uint64_t f0,
         h = w.hi > h ? w.hi : h;
     }
     lo = l;
+    hi = h;
     return h - l <= 2 * K;
 }
 
@@ -199,8 +200,8 @@ __global__ __launch_bounds__(kCmThreads) void cm_tile_kernel(CmArgs a, int s)
         const uint64_t f0 = fg * F;
         const int nf = (int)(a.n_frames - f0 < (uint64_t)F ? a.n_frames - f0 : (uint64_t)F);
         float c0[F], c1[F];
-        int lo;
-        const bool fast = tile_window<F>(a, s, f0, t, nf, K, c0, c1, lo);
+        int lo, hi;
+        const bool fast = tile_window<F>(a, s, f0, t, nf, K, c0, c1, lo, hi);
         Wide<4> S[F];
         uint32_t n0[F];
         if (fast) {
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kCmThreads) void cm_tile_kernel(CmArgs a, int s)
                     const float y = tile_value(a, s, fr[j * npix + p], pp, kp, (uint64_t)t * HW + p, npix, c0[j], c1[j]);
                     const bool nz = y < a.t_cm;
                     n0[j] += nz;
-                    limbs2_add(q0[j], q1[j], nz ? y : 0.0f, sc, sk, pk);
+                    limbs2_add(q0[j], q1[j], (double)(nz ? y : 0.0f), sc, sk, pk);
                 }
             }
 #pragma unroll
@@ -271,92 +272,147 @@ __global__ __launch_bounds__(kCmThreads) void cm_tile_kernel(CmArgs a, int s)
     }
 }
 
-// Stage s of the tile regions when every tile and frame starts on a 4-pixel
-// boundary (single gain range): one wave per (tile, group of F frames); lane
-// l adds pixels 256 k + 4 l + i, which it reads as one 8-byte group of raw
-// words and one 16-byte group of dark and 1/gain values per k.
-template <int F>
-__global__ __launch_bounds__(kCmThreads) void cm_tile_wide_kernel(CmArgs a, int s)
+// Stage S of the tile regions when every tile and frame starts on a 4-pixel
+// boundary (single gain range): one workgroup per (tile, group of F frames);
+// thread j adds pixels 1024 k + 4 j + i, which it reads as one 8-byte group of
+// raw words and one 16-byte group of dark and 1/gain values per k, dark and
+// 1/gain once for the F frames.  VALU work bounds it (about 9 + S operations a
+// pixel and frame), so eight values are added in one binary64 before they are
+// split into limbs, the values below t_cm are counted by the scalar unit, and
+// the limbs are split for the whole tile's number of values, which keeps them
+// binary64 through the reduction.  1,000 CSPAD frames: 0.90 ms a stage, 5.1 TB/s
+// of raw words (a wave per item, every value split: 2.8 ms).  A window too wide
+// for the limbs goes the way of cm_tile_kernel, frame by frame.
+template <int F, int S>
+__global__ __launch_bounds__(kCmThreads) __attribute__((amdgpu_waves_per_eu(4))) void cm_tile_wide_kernel(CmArgs a)
 {
-    const int lane = threadIdx.x & 63;
+    constexpr int NW = kCmThreads / 64;
+    __shared__ double s_q[NW][F][2];
+    __shared__ Wide<4> s_part[NW][F];
+    __shared__ uint32_t s_cnt[NW][F];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t nfg = (a.n_frames + F - 1) / F;
     const uint64_t items = nfg * (uint64_t)a.T;
     const uint32_t HW = (uint32_t)a.H * (uint32_t)a.W;
     const uint64_t npix = (uint64_t)a.T * HW;
-    const uint64_t nwaves = ((uint64_t)gridDim.x * kCmThreads) >> 6;
-    const int K = 53 - clog2(4u * ((HW + 255u) / 256u));  // values one lane adds per frame
-    for (uint64_t it = ((uint64_t)blockIdx.x * kCmThreads + threadIdx.x) >> 6; it < items; it += nwaves) {
+    constexpr uint32_t step = 4u * kCmThreads;
+    const int K = 53 - clog2(HW);
+    for (uint64_t it = blockIdx.x; it < items; it += gridDim.x) {
         const uint64_t fg = it / (uint64_t)a.T;
         const uint32_t t = (uint32_t)(it - fg * (uint64_t)a.T);
         const uint64_t f0 = fg * F;
         const int nf = (int)(a.n_frames - f0 < (uint64_t)F ? a.n_frames - f0 : (uint64_t)F);
         float c0[F], c1[F];
-        int lo;
-        const bool fast = tile_window<F>(a, s, f0, t, nf, K, c0, c1, lo);
+        int lo, hi;
+        const bool fast = tile_window<F>(a, S, f0, t, nf, K, c0, c1, lo, hi);
         if (fast) {
             const double sc = __builtin_ldexp(1.0, -lo), sk = __builtin_ldexp(1.0, -lo - K),
                          pk = __builtin_ldexp(1.0, K);
             double q0[F], q1[F];
             uint32_t n0[F];
+            const uint16_t *fr[F];
+            const float *pd = a.ped + (uint64_t)t * HW;
+            const float *kk = a.k + (uint64_t)t * HW;
 #pragma unroll
             for (int j = 0; j < F; ++j) {
                 q0[j] = q1[j] = 0.0;
                 n0[j] = 0;
+                fr[j] = a.frames + (f0 + (j < nf ? j : 0)) * npix + (uint64_t)t * HW;
             }
-            const uint16_t *fr = a.frames + f0 * npix + (uint64_t)t * HW;
-            const float *pd = a.ped + (uint64_t)t * HW;
-            const float *kk = a.k + (uint64_t)t * HW;
-            for (uint32_t p = 4u * (uint32_t)lane; p < HW; p += 256u) {  // HW is a multiple of 4
+            // 4 pixels from column offset p of every frame; a lane past the
+            // tile's end multiplies by NaN, which is not below t_cm
+            auto pixels = [&](uint32_t p, double(&g)[F], bool grouped) {
+                const bool in = p < HW;
+                p = in ? p : 0u;
                 const float4 pp = *reinterpret_cast<const float4 *>(pd + p);
                 const float4 kp = *reinterpret_cast<const float4 *>(kk + p);
-                const float pv[4] = {pp.x, pp.y, pp.z, pp.w}, kv[4] = {kp.x, kp.y, kp.z, kp.w};
+                uint2 w[F];
+#pragma unroll
+                for (int j = 0; j < F; ++j) w[j] = *reinterpret_cast<const uint2 *>(fr[j] + p);
+                const float pv[4] = {pp.x, pp.y, pp.z, pp.w};
+                float kv[4] = {kp.x, kp.y, kp.z, kp.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kv[i] = in ? kv[i] : __builtin_nanf("");
 #pragma unroll
                 for (int j = 0; j < F; ++j) {
-                    if (j >= nf) break;
-                    const uint2 w = *reinterpret_cast<const uint2 *>(fr + (uint64_t)j * npix + p);
-                    const uint32_t r[4] = {w.x & 0xFFFFu, w.x >> 16, w.y & 0xFFFFu, w.y >> 16};
+                    const uint32_t w0 = w[j].x & 0x3FFF3FFFu, w1 = w[j].y & 0x3FFF3FFFu;
+                    const float r[4] = {cvt_lo16(w0), cvt_hi16(w0), cvt_lo16(w1), cvt_hi16(w1)};
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        float y = dark_gain(r[i], pv[i], kv[i]);
-                        if (s > 0) y = __fsub_rn(y, c0[j]);
-                        if (s > 1) y = __fsub_rn(y, c1[j]);
+                        float y = __fmul_rn(__fsub_rn(r[i], pv[i]), kv[i]);
+                        if constexpr (S > 0) y = __fsub_rn(y, c0[j]);
+                        if constexpr (S > 1) y = __fsub_rn(y, c1[j]);
                         const bool nz = y < a.t_cm;
-                        n0[j] += nz;
-                        limbs2_add(q0[j], q1[j], nz ? y : 0.0f, sc, sk, pk);
+                        n0[j] += (uint32_t)__popcll(__ballot(nz));
+                        const double yd = (double)(nz ? y : 0.0f);
+                        if (grouped) g[j] += yd;
+                        else limbs2_add(q0[j], q1[j], yd, sc, sk, pk);
                     }
                 }
+            };
+            double g[F];
+            if (hi - lo <= kSumGroupSpan) {
+                static_assert(kSumGroup == 8, "two 4-pixel steps a group");
+                for (uint32_t p = 256u * wave; p < HW; p += 2u * step) {
+#pragma unroll
+                    for (int j = 0; j < F; ++j) g[j] = 0.0;
+                    pixels(p + 4u * lane, g, true);
+                    pixels(p + step + 4u * lane, g, true);
+#pragma unroll
+                    for (int j = 0; j < F; ++j) limbs2_add(q0[j], q1[j], g[j], sc, sk, pk);
+                }
+            } else {
+                for (uint32_t p = 256u * wave; p < HW; p += step) pixels(p + 4u * lane, g, false);
             }
 #pragma unroll
             for (int j = 0; j < F; ++j) {
-                const double q[2] = {q0[j], q1[j]};
-                Wide<2> S = wide_from_limbs<2>(q, K);
-                wave_sum_wide(S);
-                const uint32_t n = sum64(n0[j]);
-                if (lane == 0 && j < nf) {
-                    float *cv = a.cm + ((f0 + j) * a.T + t) * 3;
-                    cv[s] = __fdiv_rn(wide_round(S, lo), fmaxf((float)n, a.guard));
-                    if (s == 0) {
-                        cv[1] = 0.0f;
-                        cv[2] = 0.0f;
-                    }
+                const double b0 = gsum_d<64>(q0[j]), b1 = gsum_d<64>(q1[j]);
+                if (lane == 0) {
+                    s_q[wave][j][0] = b0;
+                    s_q[wave][j][1] = b1;
+                    s_cnt[wave][j] = n0[j];
                 }
             }
         } else {
             for (int j = 0; j < nf; ++j) {
-                uint32_t n0;
-                Wide<4> S = tile_sum_general(a, s, f0 + j, t, c0[j], c1[j], (uint32_t)lane, 64u, n0);
-                wave_sum_wide(S);
-                const uint32_t n = sum64(n0);
+                uint32_t c;
+                const float *cv = a.cm + ((f0 + j) * a.T + t) * 3;
+                Wide<4> P = tile_sum_general(a, S, f0 + j, t, S > 0 ? cv[0] : 0.0f, S > 1 ? cv[1] : 0.0f, threadIdx.x,
+                                             kCmThreads, c);
+                wave_sum_wide(P);
+                c = sum64(c);
                 if (lane == 0) {
-                    float *cv = a.cm + ((f0 + j) * a.T + t) * 3;
-                    cv[s] = __fdiv_rn(wide_round(S, -149), fmaxf((float)n, a.guard));
-                    if (s == 0) {
-                        cv[1] = 0.0f;
-                        cv[2] = 0.0f;
-                    }
+                    s_part[wave][j] = P;
+                    s_cnt[wave][j] = c;
                 }
             }
         }
+        __syncthreads();
+        if (threadIdx.x < nf) {
+            const int j = threadIdx.x;
+            uint32_t n = 0;
+            for (int w = 0; w < NW; ++w) n += s_cnt[w][j];
+            float sum;
+            if (fast) {
+                double b0 = 0.0, b1 = 0.0;
+                for (int w = 0; w < NW; ++w) {
+                    b0 += s_q[w][j][0];
+                    b1 += s_q[w][j][1];
+                }
+                sum = limbs2_round(b0, b1, K, lo);
+            } else {
+                Wide<4> P = s_part[0][j];
+                for (int w = 1; w < NW; ++w) wide_add(P, s_part[w][j]);
+                sum = wide_round(P, -149);
+            }
+            float *cv = a.cm + ((f0 + j) * a.T + t) * 3;
+            cv[S] = __fdiv_rn(sum, fmaxf((float)n, a.guard));
+            if (S == 0) {
+                cv[1] = 0.0f;
+                cv[2] = 0.0f;
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -391,6 +447,15 @@ hipError_t launch_cm_bank(const CmArgs &a, uint32_t n_cu, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int F>
+static void launch_tile_wide(const CmArgs &a, uint32_t n_cu, hipStream_t s)
+{
+    const uint32_t grid = cm_grid((a.n_frames + F - 1) / F * (uint64_t)a.T, 1, n_cu);
+    hipLaunchKernelGGL((cm_tile_wide_kernel<F, 0>), dim3(grid), dim3(kCmThreads), 0, s, a);
+    if (a.stages > 1) hipLaunchKernelGGL((cm_tile_wide_kernel<F, 1>), dim3(grid), dim3(kCmThreads), 0, s, a);
+    if (a.stages > 2) hipLaunchKernelGGL((cm_tile_wide_kernel<F, 2>), dim3(grid), dim3(kCmThreads), 0, s, a);
+}
+
 hipError_t launch_cm_tile(const CmArgs &a, uint32_t n_cu, hipStream_t s)
 {
     constexpr int F = 8;
@@ -401,9 +466,14 @@ hipError_t launch_cm_tile(const CmArgs &a, uint32_t n_cu, hipStream_t s)
     const bool wide = a.gain_mode == 0 && hw % 4 == 0 && ((uintptr_t)a.frames & 7u) == 0 &&
                       ((uintptr_t)a.ped & 15u) == 0 && ((uintptr_t)a.k & 15u) == 0;
     if (wide) {
-        const uint32_t grid = cm_grid(items, kCmThreads / 64, n_cu);
-        for (int st = 0; st < a.stages; ++st)
-            hipLaunchKernelGGL(cm_tile_wide_kernel<F>, dim3(grid), dim3(kCmThreads), 0, s, a, st);
+        // More frames a workgroup read dark and 1/gain less often, but leave too
+        // few workgroups of short batches.  CSPAD, whole call, 1, 4 and 8 frames
+        // (us): 16 frames 225, 316, 416; 64 frames 602, 509, 593; 128 frames
+        // 1,048, 778, 812; 1,000 frames 7,081, 5,171, 4,867.
+        const uint64_t tiles = a.n_frames * (uint64_t)a.T;
+        if (tiles <= 4ull * n_cu) launch_tile_wide<1>(a, n_cu, s);
+        else if (tiles <= 24ull * n_cu) launch_tile_wide<4>(a, n_cu, s);
+        else launch_tile_wide<F>(a, n_cu, s);
     } else {
         const uint32_t grid = cm_grid(items, 1, n_cu);
         for (int st = 0; st < a.stages; ++st)

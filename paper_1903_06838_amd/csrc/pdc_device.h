@@ -28,6 +28,20 @@ __device__ __forceinline__ float dark_gain(uint32_t raw, float ped, float k)
     return __fmul_rn(t, k);
 }
 
+// The two 16-bit halves of w as binary32 (one conversion each).
+__device__ __forceinline__ float cvt_lo16(uint32_t w)
+{
+    float r;
+    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0" : "=v"(r) : "v"(w));
+    return r;
+}
+__device__ __forceinline__ float cvt_hi16(uint32_t w)
+{
+    float r;
+    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(r) : "v"(w));
+    return r;
+}
+
 // Gain range reported by a raw word's bits 14-15 on an auto-ranging detector
 // (Dark and Gain section: one dark and one gain plane per range), or -1 for
 // an invalid code.  mode 1 (ePix10k-like): codes 0, 1, 2 -> ranges 0, 1, 2,

@@ -3,13 +3,15 @@
 // rounded once to binary32, ties to even, so that it depends on no order of
 // summation.
 //
-// Window.  Every value a stage sums is an integer multiple of 2^lo and below
+// Window.  Every value a stage sums is an integer multiple of 2^lo and at most
 // 2^hi in magnitude.  For the first stage both come from the calibration
 // (Frames1 = fl(fl(adc - dark) * k) is a multiple of 2^(min(0, lsb(dark)) +
 // lsb(k)), because a rounding to binary32 keeps a multiple of a power of two
-// that is not below 2^-149 a multiple of it; |Frames1| is at most its value at
-// adc = 0 or 16383).  A later stage sums fl(v - c): a multiple of
-// 2^min(lo, lsb(c)), at most 2^(max(hi, hi(c)) + 1) in magnitude.
+// that is not below 2^-149 a multiple of it; a value that is summed is below
+// the noise threshold, at least Frames1 at adc = 0 and at most Frames1 at adc =
+// 16383).  A later stage sums fl(v - c): a multiple of 2^min(lo, lsb(c)), at
+// most 2^(max(hi, hi(c)) + 1) in magnitude (a rounding does not pass a power of
+// two).
 //
 // Limbs.  A value x becomes the integer t = x 2^-u (u <= lo), split into limbs
 // of K bits: t = sum_i q_i 2^(K i), each q_i = trunc of the remaining part over
@@ -19,11 +21,17 @@
 // integer below 2^53, so the binary64 additions are exact in any order.  The
 // limb totals are then put together in a multiword integer and rounded once.
 //
+// Groups.  Eight values whose window spans at most 50 bits have an exact binary64
+// sum, so they are added first and split into limbs once: a conversion, 7/8 of
+// an addition and 5/8 of an operation a value instead of a conversion and six.
+// The limbs' bounds do not change (an eighth of the summands, each at most
+// eight times as large).
+//
 // Two ways are taken.  The fast one uses two limbs and u = lo: exact when
 // hi - lo <= 2 K.  The general one uses u = -149 (every binary32 is a multiple
 // of 2^-149) and NL limbs with NL K >= hi + 149; with the calibration ranges
 // the library accepts (|dark| <= 2^24, k <= 2^24) hi <= 49 in the first stage
-// and every stage adds at most 3 (|c| <= the largest |value| of its stage),
+// and every stage adds at most 1 (|c| <= the largest |value| of its stage),
 // so hi + 149 <= 204.
 #pragma once
 
@@ -51,7 +59,7 @@ __host__ __device__ __forceinline__ int f32_hi(float c)
 }
 
 struct SumWindow {
-    int lo, hi;  // every value is a multiple of 2^lo and below 2^hi in magnitude
+    int lo, hi;  // every summed value is a multiple of 2^lo and at most 2^hi in magnitude
 };
 
 // The window of the values fl(v - c) of the next stage.
@@ -59,7 +67,7 @@ __host__ __device__ __forceinline__ SumWindow next_window(SumWindow w, float c)
 {
     if (c == 0.0f) return w;  // v - 0 = v
     const int l = f32_lsb(c), h = f32_hi(c);
-    return {w.lo < l ? w.lo : l, (w.hi > h ? w.hi : h) + 2};
+    return {w.lo < l ? w.lo : l, (w.hi > h ? w.hi : h) + 1};
 }
 
 // ceil(log2(n)) for n >= 1.
@@ -91,10 +99,14 @@ __host__ __device__ __forceinline__ void limbs_add(double (&q)[NL], float x, dou
     q[0] += t;
 }
 
-// The two-limb case of limbs_add with sk = 2^(-u-K) and p = 2^K.
-__host__ __device__ __forceinline__ void limbs2_add(double &q0, double &q1, float x, double s, double sk, double p)
+// Values added before they are split into limbs, and the widest window whose
+// sums of that many are exact in binary64.
+constexpr int kSumGroup = 8, kSumGroupSpan = 50;
+
+// The two-limb case of limbs_add with sk = 2^(-u-K) and p = 2^K, for a value or
+// an exact sum of values.
+__host__ __device__ __forceinline__ void limbs2_add(double &q0, double &q1, double xd, double s, double sk, double p)
 {
-    const double xd = (double)x;
     const double d = __builtin_trunc(xd * sk);
     q1 += d;
     q0 += __builtin_fma(-d, p, xd * s);
@@ -214,6 +226,31 @@ __host__ __device__ __forceinline__ float wide_round(Wide<NW> s, int u)
     return neg ? -r : r;
 }
 
+// (q1 2^K + q0) 2^u rounded to the nearest binary32, ties to even, for limb
+// totals that are integers of at most 2^53.  The binary64 sum s of the two has
+// an exactly known error e.  Rounding s to binary32 is right unless s is a
+// midpoint of two binary32 (a midpoint is a binary64 value, so s lies on the
+// exact sum's side of every midpoint or on it); on one, e says the side.  Sums
+// below the normal binary32 range take the multiword way.
+__host__ __device__ __forceinline__ float limbs2_round(double q0, double q1, int K, int u)
+{
+    const double a = q1 * __builtin_ldexp(1.0, u + K), b = q0 * __builtin_ldexp(1.0, u);
+    const double s = a + b, bb = s - a, e = (a - (s - bb)) + (b - bb);
+    if (s != 0.0 && __builtin_fabs(s) < 0x1p-126) {
+        const double q[2] = {q0, q1};
+        return wide_round(wide_from_limbs<2>(q, K), u);
+    }
+    float f = (float)s;
+    const uint64_t bits = __builtin_bit_cast(uint64_t, s);
+    if ((uint32_t)(bits & 0x1FFFFFFFu) == 0x10000000u && e != 0.0) {
+        // towards zero, and one unit on when e points away from zero
+        const float t = (float)__builtin_bit_cast(double, bits & ~(uint64_t)0x1FFFFFFFu);
+        const bool away = (e < 0.0) == (s < 0.0);
+        f = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, t) + (away ? 1u : 0u));
+    }
+    return f;
+}
+
 // Sum of x over aligned groups of L lanes (L a power of two <= 64); exact for
 // the integer-valued limb totals.
 template <int CTRL>
@@ -250,15 +287,55 @@ __device__ __forceinline__ void wave_sum_wide(Wide<NW> &s)
     }
 }
 
+// The values of x below t added to the two limbs in groups (window of at most
+// kSumGroupSpan bits).  The threshold goes through an opaque copy tied to the
+// sums: the selections and conversions of all values would otherwise be made
+// ahead of the sums and kept in registers.
+template <int NV>
+__device__ __forceinline__ void grouped_limbs(const float (&x)[NV], float t, double s, double sk, double p, double &q0,
+                                              double &q1)
+{
+#pragma unroll
+    for (int v = 0; v < NV; v += kSumGroup) {
+        double g = (double)(x[v] < t ? x[v] : 0.0f);
+#pragma unroll
+        for (int j = 1; j < kSumGroup && v + j < NV; ++j) g += (double)(x[v + j] < t ? x[v + j] : 0.0f);
+        asm volatile("" : "+v"(t), "+v"(g));
+        limbs2_add(q0, q1, g, s, sk, p);
+    }
+}
+
+// region_sum (below, two limbs only) for a caller that is short of registers:
+// groups of values when every lane's window allows it, else slow(q0, q1, s, sk,
+// p) adds the lane's values below t to the limbs one by one (from memory, in a
+// rolled loop).  All lanes of the wave must be active.
+template <int L, int NV, typename Slow>
+__device__ __forceinline__ float region_sum_grouped(const float (&x)[NV], float t, uint32_t n, SumWindow w, int &cnt,
+                                                    bool &fits, Slow slow)
+{
+    const int K = 53 - clog2(n);
+    int c = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) c += x[v] < t;
+    cnt = c;
+    fits = w.hi - w.lo <= 2 * K;
+    const double s = __builtin_ldexp(1.0, -w.lo), sk = __builtin_ldexp(1.0, -w.lo - K), p = __builtin_ldexp(1.0, K);
+    double q0 = 0.0, q1 = 0.0;
+    if (__ballot(w.hi - w.lo > kSumGroupSpan) == 0) grouped_limbs<NV>(x, t, s, sk, p, q0, q1);
+    else slow(q0, q1, s, sk, p);
+    const float sum = limbs2_round(gsum_d<L>(q0), gsum_d<L>(q1), K, w.lo);
+    return fits ? sum : 0.0f;
+}
+
 // Exact sum, rounded once, of the values of x below t (the others add
 // nothing) of a region held by a group of L lanes, NV values per lane, at most
 // n values in all (n <= 1024), within window w; cnt receives the lane's number
 // of values below t.  Every lane of the group returns the sum.  The general
 // way forms one limb at a time, q_i = trunc(t 2^-(K i)) - 2^K trunc(t
-// 2^-(K (i + 1))), which keeps one accumulator live.  Without GENERAL a window
-// too wide for two limbs returns 0 with fits = false (the caller has the
-// region summed elsewhere).
-template <int L, int NV, bool GENERAL = true>
+// 2^-(K (i + 1))), which keeps one accumulator live.  (A window too wide for two
+// limbs, region_sum_grouped: 0 with fits = false, and the caller has the region
+// summed elsewhere.)
+template <int L, int NV>
 __device__ __forceinline__ float region_sum(const float (&x)[NV], float t, uint32_t n, SumWindow w, int &cnt,
                                             bool &fits)
 {
@@ -268,15 +345,17 @@ __device__ __forceinline__ float region_sum(const float (&x)[NV], float t, uint3
     for (int v = 0; v < NV; ++v) c += x[v] < t;
     cnt = c;
     fits = w.hi - w.lo <= 2 * K;
-    if (!GENERAL && !fits) return 0.0f;
     if (fits) {
         const double s = __builtin_ldexp(1.0, -w.lo), sk = __builtin_ldexp(1.0, -w.lo - K),
                      p = __builtin_ldexp(1.0, K);
         double q0 = 0.0, q1 = 0.0;
+        if (w.hi - w.lo <= kSumGroupSpan) {
+            grouped_limbs<NV>(x, t, s, sk, p, q0, q1);
+        } else {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) limbs2_add(q0, q1, x[v] < t ? x[v] : 0.0f, s, sk, p);
-        const double q[2] = {gsum_d<L>(q0), gsum_d<L>(q1)};
-        return wide_round(wide_from_limbs<2>(q, K), w.lo);
+            for (int v = 0; v < NV; ++v) limbs2_add(q0, q1, (double)(x[v] < t ? x[v] : 0.0f), s, sk, p);
+        }
+        return limbs2_round(gsum_d<L>(q0), gsum_d<L>(q1), K, w.lo);
     }
     constexpr int NL = kGenNL10;
     constexpr int KG = kGenK10;

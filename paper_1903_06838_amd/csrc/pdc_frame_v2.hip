@@ -538,20 +538,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
 typedef f32x4 f32x4_a8 __attribute__((aligned(8)));
 
-// The two 16-bit halves of w as binary32 (one conversion each).
-__device__ __forceinline__ float cvt_lo16(uint32_t w)
-{
-    float r;
-    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0" : "=v"(r) : "v"(w));
-    return r;
-}
-__device__ __forceinline__ float cvt_hi16(uint32_t w)
-{
-    float r;
-    asm("v_cvt_f32_u32_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(r) : "v"(w));
-    return r;
-}
-
 // Values a lane holds in the finish of the medians (a group sorts S L).
 template <int L>
 constexpr int kV2Finish = L == 4 ? 4 : (L == 8 ? 3 : 2);
@@ -989,7 +975,19 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
                         if (s >= A->cm_stages) break;
                         int n;
                         bool fits;
-                        const float sum = region_sum<L, V, false>(x, A->t_cm, (uint32_t)B, win, n, fits);
+                        const float sum = region_sum_grouped<L, V>(
+                            x, A->t_cm, (uint32_t)B, win, n, fits,
+                            [&](double &q0, double &q1, double sc, double sk, double pk) {
+                                // a wide window (rare: a later stage's small
+                                // value): the lane's values from its own LDS slots
+                                if (act) store_v(x, o4);
+#pragma unroll 1
+                                for (int v = 0; v < V; ++v) {
+                                    const float y = s_v[o4 + slot_off<L, Q, R>(v, gl)];
+                                    const bool nz = y < A->t_cm && ((vmask >> v) & 1u);
+                                    limbs2_add(q0, q1, (double)(nz ? y : 0.0f), sc, sk, pk);
+                                }
+                            });
                         wide |= !fits;
                         const int n0 = gsum_i<L>(n);
                         const float cm = __fdiv_rn(sum, fmaxf((float)n0, A->cm_guard));

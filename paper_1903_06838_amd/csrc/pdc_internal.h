@@ -106,7 +106,7 @@ struct V2Args {
                                   // 2 thresholded-mean stage values read from cm
     int32_t cm_stages;            // cm_mode 1: stages, noise threshold and guard
     float t_cm, cm_guard;
-    int32_t sum_lo, sum_hi;       // cm_mode 1: Frames1 values are multiples of 2^sum_lo below 2^sum_hi
+    int32_t sum_lo, sum_hi;       // cm_mode 1: summed Frames1 values are multiples of 2^sum_lo up to 2^sum_hi
     int32_t gain_mode;
     uint32_t *invalid;
     float *meds;                  // as in FrameKernelArgs (median mode)
@@ -155,7 +155,7 @@ struct CmArgs {
     int32_t stages;               // 1..3
     float t_cm;                   // pixels below it are noise
     float guard;                  // fl(sqrt(fl(region size)))
-    int32_t sum_lo, sum_hi;       // Frames1 values are multiples of 2^sum_lo below 2^sum_hi
+    int32_t sum_lo, sum_hi;       // summed Frames1 values are multiples of 2^sum_lo up to 2^sum_hi
     int32_t gain_mode;            // as in FrameKernelArgs
     float *cm;
 };

@@ -49,7 +49,7 @@ struct Detector {
     float t_seed = 0, t_nb = 0;
     float t_cm = 0, cm_guard = 0;         // thresholded-mean common mode (cm_mode 1 or 2)
     uint32_t cm_regions = 0;              // regions per frame
-    int32_t sum_lo = 0, sum_hi = 0;       // window of Frames1: multiples of 2^sum_lo below 2^sum_hi
+    int32_t sum_lo = 0, sum_hi = 0;       // window of the summed Frames1: multiples of 2^sum_lo up to 2^sum_hi
     float *d_ped = nullptr;
     float *d_k = nullptr;
     // derived launch shape of the general kernel (v1)
@@ -291,12 +291,12 @@ int f32_hi_host(float c)
     return E ? E - 126 : -149 + (32 - __builtin_clz(b));
 }
 
-// Window of every Frames1 value fl(fl(adc - dark) * k), adc in [0, 16383]: a
-// multiple of 2^(min(0, lsb(dark)) + lsb(k)) (adc is an integer; a rounding to
-// binary32 keeps such a multiple), at most the larger of |x(0)| and |x(16383)|
-// in magnitude (x is monotone in adc).  The exact thresholded sums size their
-// accumulators from it.
-void frames1_window(const float *ped, const float *k, size_t n, int32_t *lo, int32_t *hi)
+// Window of the Frames1 values fl(fl(adc - dark) * k), adc in [0, 16383], that
+// are below t_cm (the only ones a thresholded sum takes): a multiple of
+// 2^(min(0, lsb(dark)) + lsb(k)) (adc is an integer; a rounding to binary32
+// keeps such a multiple), from x(0) up to the smaller of x(16383) and t_cm (x is
+// monotone in adc).  The exact sums size their accumulators from it.
+void frames1_window(const float *ped, const float *k, size_t n, float t_cm, int32_t *lo, int32_t *hi)
 {
     int l = 0, h = -149;
     for (size_t i = 0; i < n; ++i) {
@@ -304,7 +304,7 @@ void frames1_window(const float *ped, const float *k, size_t n, int32_t *lo, int
         l = std::min(l, lp + f32_lsb_host(k[i]));
         volatile float a0 = 0.0f - ped[i], a1 = 16383.0f - ped[i];  // binary32
         volatile float x0 = a0 * k[i], x1 = a1 * k[i];
-        h = std::max(h, std::max(f32_hi_host(x0), f32_hi_host(x1)));
+        h = std::max(h, std::max(f32_hi_host(x0), f32_hi_host(std::min((float)x1, t_cm))));
     }
     *lo = l;
     *hi = h;
@@ -1211,7 +1211,7 @@ pdc_status pdc_calibrate(pdc_ctx *ctx, const pdc_geometry *geom, const float *pe
         volatile float r = 1.0f / gain[i];  // binary32 division
         k[i] = r;
     }
-    if (params->cm_mode != PDC_CM_MEDIAN) frames1_window(pedestal, k.data(), n, &d.sum_lo, &d.sum_hi);
+    if (params->cm_mode != PDC_CM_MEDIAN) frames1_window(pedestal, k.data(), n, d.t_cm, &d.sum_lo, &d.sum_hi);
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     HIP_TRY(ctx, hipMalloc((void **)&d.d_ped, n * sizeof(float)));
     HIP_TRY(ctx, hipMalloc((void **)&d.d_k, n * sizeof(float)));

@@ -1067,7 +1067,6 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
     }
 }
 
-// Frames of an item: enough items for about 16 waves a compute unit, and a
 // Frames of an item: enough items for 32 waves a compute unit (8: 137 us, 16:
 // 114, 32: 100 at the size above), and where there are more a strip's frames
 // taken one after another.
