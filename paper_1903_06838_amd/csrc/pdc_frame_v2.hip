@@ -33,6 +33,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "pdc_device.h"
 #include "pdc_exact.h"
 #include "pdc_internal.h"
@@ -533,10 +535,13 @@ __device__ __forceinline__ int block_item(int b, int n)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-// raw words are read, and u written, at 4- and 8-byte alignment (a bank may
-// start at any even column)
+// raw words are read, and u written, at 4- and 8-byte alignment (a bank of an
+// even width starts at an even column), with an odd width at 2 and 4 bytes
 typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 typedef f32x4 f32x4_a8 __attribute__((aligned(8)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+typedef uint32_t u32_a2 __attribute__((aligned(2)));
 
 // Values a lane holds in the finish of the medians (a group sorts S L).
 template <int L>
@@ -561,14 +566,17 @@ __device__ __forceinline__ V2ArgsK fresh(V2ArgsK a)
 }
 
 // One workgroup's work: work item `item` of the launch over A's strips and
-// frame groups (strip item % n_strips, frame group item / n_strips).
-template <int L, int Q, int R, bool KEEP, int CMM, bool MG>
+// frame groups (strip item % n_strips, frame group item / n_strips).  ODD: banks
+// of an odd width, whose last column has no partner.
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
 __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
 {
     constexpr int V = 8 * Q + R, G = 64 / L, S = kV2Finish<L>, P = kV2Passes<L>;
     constexpr int kCntRegs = (kV2Threads / L * P + 63) / 64;  // bank-rows of a workgroup, 64 a register
     constexpr int kBitWords = (8 * L * Q + L * R + 31) / 32;  // of the widest bank of this layout
     static_assert(V <= 32, "a lane's values are bits of one mask");
+    using raw4 = std::conditional_t<ODD, u32x4_a2, u32x4_a4>;
+    using val4 = std::conditional_t<ODD, f32x4_a4, f32x4_a8>;
     extern __shared__ __align__(16) float lds[];
 #ifdef PDC_PHASE_TIMERS
     __shared__ unsigned long long s_tm[kV2Waves * 8];
@@ -645,8 +653,8 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
             const int o = slot_off<L, Q, R>(v, gl);
             f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = a;
             if (quads) {
-                a = *reinterpret_cast<const f32x4_a8 *>(pp + o);
-                b = *reinterpret_cast<const f32x4_a8 *>(kp + o);
+                a = *reinterpret_cast<const val4 *>(pp + o);
+                b = *reinterpret_cast<const val4 *>(kp + o);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -691,15 +699,30 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
         for (int r = 0; r < (R > 0 ? R : 1); ++r) rawt_[p][r] = 0u;
     }
     const uint16_t *fr_next = A->frames + f_begin * npix + row_base;  // strip of the next frame to load
+    auto chunk_in = [&](int c) { return ((vmask >> (8 * c)) & 0xFFu) == 0xFFu; };  // columns 8 c .. of the lane
     auto load_raw = [&](const uint16_t *fr, int o4, u32x4(&raw)[Q], uint32_t(&rawt)[R > 0 ? R : 1]) {
         if (full) {
 #pragma unroll
             for (int c = 0; c < Q; ++c)
-                raw[c] = *reinterpret_cast<const u32x4_a4 *>(fr + (uint32_t)o4 + 8 * L * c);
+                raw[c] = *reinterpret_cast<const raw4 *>(fr + (uint32_t)o4 + 8 * L * c);
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if ((vmask >> (8 * Q + r)) & 1u)
                     rawt[r] = fr[(uint32_t)(o4 + slot_off<L, Q, R>(8 * Q + r, gl))];
+        } else if constexpr (ODD) {
+#pragma unroll
+            for (int c = 0; c < Q; ++c) {
+                const uint16_t *p = fr + (uint32_t)o4 + 8 * L * c;
+                if (chunk_in(c)) {
+                    raw[c] = *reinterpret_cast<const raw4 *>(p);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if ((vmask >> (8 * c + 2 * j + 1)) & 1u) raw[c][j] = *reinterpret_cast<const u32_a2 *>(p + 2 * j);
+                        else if ((vmask >> (8 * c + 2 * j)) & 1u) raw[c][j] = p[2 * j];
+                    }
+                }
+            }
         } else {
 #pragma unroll
             for (int c = 0; c < Q; ++c) {
@@ -710,17 +733,35 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
             }
         }
     };
+    // an odd bank's values to memory: whole groups of 8 slots, else one by one
+    auto store_odd = [&](float *dst, const float(&x)[V]) {
+#pragma unroll
+        for (int c = 0; c < Q; ++c) {
+            if (chunk_in(c)) {
+#pragma unroll
+                for (int h = 8 * c; h < 8 * c + 8; h += 4)
+                    *reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(h, gl)) =
+                        f32x4{x[h], x[h + 1], x[h + 2], x[h + 3]};
+            } else {
+#pragma unroll
+                for (int v = 8 * c; v < 8 * c + 8; ++v)
+                    if ((vmask >> v) & 1u) dst[slot_off<L, Q, R>(v, gl)] = x[v];
+            }
+        }
+    };
     // the lane's values to and from LDS (an active group's, slots in the bank)
     auto store_v = [&](const float(&x)[V], int o4) {
         float *dst = s_v + o4;
         if (full) {
 #pragma unroll
             for (int c = 0; c < 2 * Q; ++c)
-                *reinterpret_cast<f32x4_a8 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
+                *reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
                     f32x4{x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]};
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if ((vmask >> (8 * Q + r)) & 1u) dst[slot_off<L, Q, R>(8 * Q + r, gl)] = x[8 * Q + r];
+        } else if constexpr (ODD) {
+            store_odd(dst, x);
         } else {
 #pragma unroll
             for (int v = 0; v < 8 * Q; v += 2)
@@ -734,11 +775,13 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
         if (full) {
 #pragma unroll
             for (int c = 0; c < 2 * Q; ++c)
-                *reinterpret_cast<f32x4_a8 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
+                *reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
                     f32x4{y[4 * c], y[4 * c + 1], y[4 * c + 2], y[4 * c + 3]};
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if ((vmask >> (8 * Q + r)) & 1u) dst[slot_off<L, Q, R>(8 * Q + r, gl)] = y[8 * Q + r];
+        } else if constexpr (ODD) {
+            store_odd(dst, y);
         } else {
 #pragma unroll
             for (int v = 0; v < 8 * Q; v += 2)
@@ -1181,10 +1224,10 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
 #undef PDC_PHASE
 }
 
-template <int L, int Q, int R, bool KEEP, int CMM, bool MG>
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
 __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2(V2Args)
 {
-    frame_body<L, Q, R, KEEP, CMM, MG>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
+    frame_body<L, Q, R, KEEP, CMM, MG, ODD>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
 }
 
 // Several detectors' batches in one launch: the work items of detector d are
@@ -1237,10 +1280,10 @@ size_t v2_layout_finish_bytes(int layout)
     return (size_t)kV2Threads * 4 * (layout < 2 ? kV2Finish<4> : (layout < 4 ? kV2Finish<8> : kV2Finish<16>));
 }
 
-template <int L, int Q, int R, bool KEEP, int CMM, bool MG>
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
 static hipError_t launch_v2_k(const V2Args &a, uint32_t grid, size_t lds, hipStream_t s)
 {
-    auto k = frame_kernel_v2<L, Q, R, KEEP, CMM, MG>;
+    auto k = frame_kernel_v2<L, Q, R, KEEP, CMM, MG, ODD>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(grid), dim3(kV2Threads), lds, s, a);
@@ -1251,6 +1294,11 @@ template <int L, int Q, int R>
 static hipError_t launch_v2_t(const V2Args &a, uint32_t grid, size_t lds, bool keep, hipStream_t s)
 {
     if (a.cm_mode < 0 || a.cm_mode > 2) return hipErrorInvalidValue;
+    if (a.B & 1) {  // (the plan keeps the other odd-bank modes on the general kernel)
+        if (a.cm_mode || a.gain_mode) return hipErrorInvalidValue;
+        return keep ? launch_v2_k<L, Q, R, true, 0, false, true>(a, grid, lds, s)
+                    : launch_v2_k<L, Q, R, false, 0, false, true>(a, grid, lds, s);
+    }
     switch (a.cm_mode * 4 + (keep ? 2 : 0) + (a.gain_mode ? 1 : 0)) {
     case 0: return launch_v2_k<L, Q, R, false, 0, false>(a, grid, lds, s);
     case 1: return launch_v2_k<L, Q, R, false, 0, true>(a, grid, lds, s);
@@ -1283,7 +1331,7 @@ hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bo
 int v2_mix_variant(const V2Args &a, bool keep)
 {
     const int lay = v2_layout_of(a.B);
-    if (keep || a.cm_mode || a.meds || a.B < 1 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return -1;
+    if (keep || a.cm_mode || a.meds || a.B < 1 || (a.B & 1) || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return -1;
     return lay + (a.gain_mode ? 5 : 0);
 }
 

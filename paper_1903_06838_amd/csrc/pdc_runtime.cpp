@@ -361,16 +361,16 @@ bool plan_v1(Detector &d)
 
 // Plan of the persistent kernel: strips of at most rmax loaded rows, as many
 // strips x frame groups as there are compute units; false if the geometry is
-// outside its fast path (odd widths, banks wider than 256, or too little LDS).
+// outside its fast path (one-column banks or banks wider than 256, odd widths
+// with gain ranges or a thresholded mean, or too little LDS).  Odd widths have
+// a compiled body for the median alone: 64 frames of 8 x 185 x 194 pixels in
+// banks of 97 take it 68 us, the general kernel 624 us.
 bool plan_v2(pdc_ctx *ctx, Detector &d)
 {
     const pdc_geometry &g = d.g;
     d.v2_ok = false;
-    if ((g.cols & 1) || (g.bank_cols & 1) || g.bank_cols > 256 || g.bank_cols < 2)
-        return false;
-    // single-gain kernels read each strip as a block of 4-pixel chunks
-    if (!g.gain_mode && (g.cols % 4))
-        return false;
+    if (g.bank_cols > 256 || g.bank_cols < 2) return false;
+    if ((g.bank_cols & 1) && (g.gain_mode || d.p.cm_mode != PDC_CM_MEDIAN)) return false;
     const int nb = g.cols / g.bank_cols;
     const int layout = v2_layout_of(g.bank_cols);
     const int max_bank_rows = v2_layout_bank_rows(layout);
@@ -2389,7 +2389,9 @@ pdc_status pdc_autotune_strips(pdc_ctx *ctx, int32_t det, const uint16_t *frames
         return fail(ctx, PDC_ESTATE, "unknown detector %d", det);
     if (n_frames < 1 || !frames_dev) return fail(ctx, PDC_EINVAL, "need frames_dev and n_frames >= 1");
     Detector &d = ctx->dets[det];
-    if (!d.v2_ok) return fail(ctx, PDC_ESTATE, "the detector does not take the persistent kernel");
+    // (widths off the persistent kernel's 4-column grid keep their one strip height)
+    if (!d.v2_ok || (d.g.bank_cols & 1) || (!d.g.gain_mode && d.g.cols % 4))
+        return fail(ctx, PDC_ESTATE, "the detector does not take the tuned forms of the persistent kernel");
     if (d.pending) return fail(ctx, PDC_ESTATE, "the detector has outstanding batches or graphs");
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     // own rows per strip: the most the lane layout holds, then 4 and 8 fewer
