@@ -33,8 +33,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include <type_traits>
-
 #include "pdc_device.h"
 #include "pdc_exact.h"
 #include "pdc_internal.h"
@@ -537,10 +535,18 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 // raw words are read, and u written, at 4- and 8-byte alignment (a bank of an
 // even width starts at an even column), with an odd width at 2 and 4 bytes
-typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
-typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
-typedef f32x4 f32x4_a8 __attribute__((aligned(8)));
-typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+// (structs: an alignment on a typedef is lost where the type is a template
+// argument; 16-byte LDS stores at 8-byte alignment cost more than pairs of 8:
+// 10,000 CSPAD frames 29.4 ms against 25.9, while at 16-byte alignment they are
+// the better ones: three mixed detectors' 1,000 frames 2.60 ms against 2.70)
+template <int A>
+struct __attribute__((packed, aligned(A))) Raw4 {
+    u32x4 v;
+};
+template <int A>
+struct __attribute__((packed, aligned(A))) Val4 {
+    f32x4 v;
+};
 typedef uint32_t u32_a2 __attribute__((aligned(2)));
 
 // Values a lane holds in the finish of the medians (a group sorts S L).
@@ -575,8 +581,10 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
     constexpr int kCntRegs = (kV2Threads / L * P + 63) / 64;  // bank-rows of a workgroup, 64 a register
     constexpr int kBitWords = (8 * L * Q + L * R + 31) / 32;  // of the widest bank of this layout
     static_assert(V <= 32, "a lane's values are bits of one mask");
-    using raw4 = std::conditional_t<ODD, u32x4_a2, u32x4_a4>;
-    using val4 = std::conditional_t<ODD, f32x4_a4, f32x4_a8>;
+    using raw4 = Raw4<ODD ? 2 : 4>;
+    // (without single slots a full bank is 8 L Q columns, so every bank starts
+    // at a multiple of 4 floats: 16-byte LDS stores)
+    using val4 = Val4<ODD ? 4 : (R == 0 ? 16 : 8)>;
     extern __shared__ __align__(16) float lds[];
 #ifdef PDC_PHASE_TIMERS
     __shared__ unsigned long long s_tm[kV2Waves * 8];
@@ -653,8 +661,8 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
             const int o = slot_off<L, Q, R>(v, gl);
             f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = a;
             if (quads) {
-                a = *reinterpret_cast<const val4 *>(pp + o);
-                b = *reinterpret_cast<const val4 *>(kp + o);
+                a = reinterpret_cast<const val4 *>(pp + o)->v;
+                b = reinterpret_cast<const val4 *>(kp + o)->v;
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -704,7 +712,7 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
         if (full) {
 #pragma unroll
             for (int c = 0; c < Q; ++c)
-                raw[c] = *reinterpret_cast<const raw4 *>(fr + (uint32_t)o4 + 8 * L * c);
+                raw[c] = reinterpret_cast<const raw4 *>(fr + (uint32_t)o4 + 8 * L * c)->v;
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if ((vmask >> (8 * Q + r)) & 1u)
@@ -714,7 +722,7 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
             for (int c = 0; c < Q; ++c) {
                 const uint16_t *p = fr + (uint32_t)o4 + 8 * L * c;
                 if (chunk_in(c)) {
-                    raw[c] = *reinterpret_cast<const raw4 *>(p);
+                    raw[c] = reinterpret_cast<const raw4 *>(p)->v;
                 } else {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -740,7 +748,7 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
             if (chunk_in(c)) {
 #pragma unroll
                 for (int h = 8 * c; h < 8 * c + 8; h += 4)
-                    *reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(h, gl)) =
+                    reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(h, gl))->v =
                         f32x4{x[h], x[h + 1], x[h + 2], x[h + 3]};
             } else {
 #pragma unroll
@@ -755,7 +763,7 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
         if (full) {
 #pragma unroll
             for (int c = 0; c < 2 * Q; ++c)
-                *reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
+                reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(4 * c, gl))->v =
                     f32x4{x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]};
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -775,7 +783,7 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
         if (full) {
 #pragma unroll
             for (int c = 0; c < 2 * Q; ++c)
-                *reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(4 * c, gl)) =
+                reinterpret_cast<val4 *>(dst + slot_off<L, Q, R>(4 * c, gl))->v =
                     f32x4{y[4 * c], y[4 * c + 1], y[4 * c + 2], y[4 * c + 3]};
 #pragma unroll
             for (int r = 0; r < R; ++r)
