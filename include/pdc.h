@@ -324,10 +324,11 @@ pdc_status pdc_release_batch(pdc_ctx *ctx, uint64_t batch);
 pdc_status pdc_batch_bytes(pdc_ctx *ctx, int32_t det, uint64_t n_frames, uint64_t hit_capacity,
                            uint64_t *bytes);
 
-/* Timing of a finished batch from HIP events recorded on its stream:
- * *main_ms = the fused frame kernel alone, *total_ms = every kernel of the
- * batch (common-mode pass of the mean modes, frame kernel, scans, hit
- * scatter).  Either pointer may be NULL. */
+/* Timing of a finished batch: *main_ms = the fused frame kernel alone, from
+ * the device clock that the kernels before and after it read, *total_ms =
+ * every kernel of the batch (common-mode pass of the mean modes, frame kernel,
+ * scans, hit scatter), from HIP events recorded on its stream.  Either pointer
+ * may be NULL. */
 pdc_status pdc_batch_timing(pdc_ctx *ctx, uint64_t batch, float *main_ms, float *total_ms);
 
 /* Measurement aid: a plain streaming read of bytes (a nonzero multiple of 16)

@@ -30,6 +30,15 @@ struct BatchState {
     unsigned int fallback;        // 1 if the fast kernel left some unit to the general kernel
     unsigned long long total;     // total hits of the batch (set by the frame scan)
     unsigned long long n_fallback;  // units listed in the batch's fallback list
+    unsigned long long t0, t1;    // device clock before and after the frame kernel
+};
+
+// Pinned host copies that a batch's last kernels write themselves (NULL: none):
+// a copy engine's transfer costs a small batch more than its scans.
+struct HostMirror {
+    BatchState *state;
+    uint32_t *frame_hits;
+    unsigned long long *frame_photons;
 };
 
 // Persistent kernel (v2): a strip owns frame rows [g0, g1), counted over all
@@ -169,18 +178,39 @@ hipError_t launch_init_state(BatchState *state, hipStream_t s);
 hipError_t launch_frame_kernel_v1(const FrameKernelArgs &a, uint32_t grid, size_t lds_bytes,
                                   bool keep_corrected, hipStream_t s);
 // Per frame: in-frame exclusive offsets of units, hit counts and photon totals.
+// stamp: the frame kernel has just ended (its end time goes into state).
 hipError_t launch_frame_sums(const uint32_t *unit_count, const unsigned long long *unit_photons,
                              uint64_t n_frames, int32_t units_per_frame, uint32_t *unit_local,
-                             uint32_t *frame_hits, unsigned long long *frame_photons,
-                             hipStream_t s);
+                             uint32_t *frame_hits, unsigned long long *frame_photons, BatchState *state,
+                             HostMirror host, bool stamp, hipStream_t s);
 // Exclusive scan of frame hit counts: frame_offset[0..n_frames], total into state.
 hipError_t launch_frame_scan(const uint32_t *frame_hits, uint64_t n_frames,
-                             unsigned long long *frame_offset, BatchState *state, hipStream_t s);
+                             unsigned long long *frame_offset, BatchState *state, HostMirror host, hipStream_t s);
 // Copy each unit's staged hits to its place in the raster-order list.
 hipError_t launch_scatter(const uint32_t *unit_count, const uint64_t *unit_base,
                           const uint32_t *unit_local, const unsigned long long *frame_offset,
                           const uint2 *pool, uint64_t n_units, int32_t units_per_frame,
                           uint2 *hits, uint64_t hits_cap, hipStream_t s);
+
+// The three above in one launch, for batches of few units.
+struct TailArgs {
+    const uint32_t *unit_count;
+    const unsigned long long *unit_photons;
+    const uint64_t *unit_base;
+    uint32_t *unit_local;
+    uint32_t *frame_hits;
+    unsigned long long *frame_photons;
+    unsigned long long *frame_offset;
+    const uint2 *pool;
+    uint2 *hits;
+    uint64_t hits_cap;
+    BatchState *state;
+    HostMirror host;
+    uint32_t n_frames, n_units, upf;
+    int32_t stamp;
+};
+bool tail_fits(uint64_t n_units, int32_t upf);
+hipError_t launch_tail(const TailArgs &a, hipStream_t s);
 
 // The 16-byte hit record of the public ABI.
 struct HitRecord {

@@ -22,6 +22,7 @@ __global__ void init_state_kernel(BatchState *st)
         st->fallback = 0;
         st->total = 0;
         st->n_fallback = 0;
+        st->t0 = st->t1 = wall_clock64();
     }
 }
 
@@ -327,15 +328,24 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T *s_tmp, T *block_total)
     return off + inc - x;
 }
 
+// The batch's state to its pinned copy (one thread, after the last change).
+__device__ __forceinline__ void publish_state(const BatchState *st, const HostMirror &host)
+{
+    if (!host.state) return;
+    *host.state = *st;
+    __threadfence_system();
+}
+
 __global__ void __launch_bounds__(kScanThreads)
 frame_sums_kernel(const uint32_t *unit_count, const unsigned long long *unit_photons,
                   uint64_t n_frames, int32_t upf, uint32_t *unit_local, uint32_t *frame_hits,
-                  unsigned long long *frame_photons)
+                  unsigned long long *frame_photons, BatchState *st, HostMirror host, int stamp)
 {
     __shared__ uint32_t s_tmp[kScanThreads / 64];
     __shared__ unsigned long long s_ph;
     const uint64_t f = blockIdx.x;
     if (f >= n_frames) return;
+    if (stamp && f == 0 && threadIdx.x == 0) st->t1 = wall_clock64();
     if (threadIdx.x == 0) s_ph = 0;
     __syncthreads();
     const uint64_t u0 = f * (uint64_t)upf;
@@ -355,23 +365,29 @@ frame_sums_kernel(const uint32_t *unit_count, const unsigned long long *unit_pho
     if (threadIdx.x == 0) {
         frame_hits[f] = carry;
         frame_photons[f] = s_ph;
+        if (host.frame_hits) {
+            host.frame_hits[f] = carry;
+            host.frame_photons[f] = s_ph;
+            __threadfence_system();
+        }
     }
 }
 
 hipError_t launch_frame_sums(const uint32_t *unit_count, const unsigned long long *unit_photons,
                              uint64_t n_frames, int32_t units_per_frame, uint32_t *unit_local,
-                             uint32_t *frame_hits, unsigned long long *frame_photons, hipStream_t s)
+                             uint32_t *frame_hits, unsigned long long *frame_photons, BatchState *state,
+                             HostMirror host, bool stamp, hipStream_t s)
 {
     if (n_frames == 0) return hipSuccess;
     hipLaunchKernelGGL(frame_sums_kernel, dim3((uint32_t)n_frames), dim3(kScanThreads), 0, s,
                        unit_count, unit_photons, n_frames, units_per_frame, unit_local,
-                       frame_hits, frame_photons);
+                       frame_hits, frame_photons, state, host, stamp ? 1 : 0);
     return hipGetLastError();
 }
 
 __global__ void __launch_bounds__(kScanThreads)
 frame_scan_kernel(const uint32_t *frame_hits, uint64_t n_frames, unsigned long long *frame_offset,
-                  BatchState *st)
+                  BatchState *st, HostMirror host)
 {
     __shared__ unsigned long long s_tmp[kScanThreads / 64];
     unsigned long long carry = 0;
@@ -386,14 +402,15 @@ frame_scan_kernel(const uint32_t *frame_hits, uint64_t n_frames, unsigned long l
     if (threadIdx.x == 0) {
         frame_offset[n_frames] = carry;
         st->total = carry;
+        publish_state(st, host);
     }
 }
 
 hipError_t launch_frame_scan(const uint32_t *frame_hits, uint64_t n_frames,
-                             unsigned long long *frame_offset, BatchState *state, hipStream_t s)
+                             unsigned long long *frame_offset, BatchState *state, HostMirror host, hipStream_t s)
 {
     hipLaunchKernelGGL(frame_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, frame_hits, n_frames,
-                       frame_offset, state);
+                       frame_offset, state, host);
     return hipGetLastError();
 }
 
@@ -408,33 +425,21 @@ hipError_t launch_frame_scan(const uint32_t *frame_hits, uint64_t n_frames,
 // overflow; the batch is then recomputed) copy nothing.
 constexpr int kScatterUnits = 4;
 
-__global__ void __launch_bounds__(256)
-scatter_kernel(const uint32_t *unit_count, const uint64_t *unit_base, const uint32_t *unit_local,
-               const unsigned long long *frame_offset, const uint2 *pool, uint64_t n_units,
-               int32_t upf, uint2 *hits, uint64_t hits_cap)
+// The runs of U units held by lanes first .. first + U - 1 (count c, staging
+// place b, destination dst).
+__device__ __forceinline__ void copy_runs(uint32_t c, uint64_t b, uint64_t dst, int first, int lane, const uint2 *pool,
+                                          uint2 *hits)
 {
     constexpr int U = kScatterUnits;
-    const uint64_t u0 = ((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * U;
-    const int lane = threadIdx.x & 63;
-    if (u0 >= n_units) return;
-    uint32_t c = 0;
-    uint64_t b = 0, dst = 0;
-    if (lane < U && u0 + lane < n_units) {
-        const uint64_t unit = u0 + lane;
-        c = unit_count[unit];
-        b = unit_base[unit];
-        dst = frame_offset[unit / (uint64_t)upf] + unit_local[unit];
-        if (b == kNoBase || dst + c > hits_cap) c = 0;
-    }
     uint32_t cu[U];
     uint64_t bu[U], du[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-        cu[k] = (uint32_t)__builtin_amdgcn_readlane((int)c, k);
-        bu[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), k) << 32) |
-                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, k);
-        du[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(dst >> 32), k) << 32) |
-                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dst, k);
+        cu[k] = (uint32_t)__builtin_amdgcn_readlane((int)c, first + k);
+        bu[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), first + k) << 32) |
+                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, first + k);
+        du[k] = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(dst >> 32), first + k) << 32) |
+                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dst, first + k);
     }
     uint2 v[U][2];
 #pragma unroll
@@ -456,6 +461,28 @@ scatter_kernel(const uint32_t *unit_count, const uint64_t *unit_base, const uint
         for (uint32_t i = (uint32_t)lane + 128u; i < cu[k]; i += 64) hits[du[k] + i] = pool[bu[k] + i];
 }
 
+
+__global__ void __launch_bounds__(256)
+scatter_kernel(const uint32_t *unit_count, const uint64_t *unit_base, const uint32_t *unit_local,
+               const unsigned long long *frame_offset, const uint2 *pool, uint64_t n_units,
+               int32_t upf, uint2 *hits, uint64_t hits_cap)
+{
+    constexpr int U = kScatterUnits;
+    const uint64_t u0 = ((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * U;
+    const int lane = threadIdx.x & 63;
+    if (u0 >= n_units) return;
+    uint32_t c = 0;
+    uint64_t b = 0, dst = 0;
+    if (lane < U && u0 + lane < n_units) {
+        const uint64_t unit = u0 + lane;
+        c = unit_count[unit];
+        b = unit_base[unit];
+        dst = frame_offset[unit / (uint64_t)upf] + unit_local[unit];
+        if (b == kNoBase || dst + c > hits_cap) c = 0;
+    }
+    copy_runs(c, b, dst, 0, lane, pool, hits);
+}
+
 hipError_t launch_scatter(const uint32_t *unit_count, const uint64_t *unit_base,
                           const uint32_t *unit_local, const unsigned long long *frame_offset,
                           const uint2 *pool, uint64_t n_units, int32_t units_per_frame,
@@ -467,6 +494,108 @@ hipError_t launch_scatter(const uint32_t *unit_count, const uint64_t *unit_base,
     hipLaunchKernelGGL(scatter_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, unit_count,
                        unit_base, unit_local, frame_offset, pool, n_units, units_per_frame, hits,
                        hits_cap);
+    return hipGetLastError();
+}
+
+// frame_sums, frame_scan and scatter of a batch of few units in one launch: a
+// workgroup of 16 units sums all unit counts before its own itself (a few
+// loads a thread) instead of waiting for the scan of a launch before, forms the
+// totals of the frames that start in its units, and copies its runs.  The last
+// workgroup publishes the batch's state.  Launches and the gaps between them
+// bound such batches: 16 CSPAD frames (3,168 units) took 13 us in the three
+// kernels and 10 us more for a copy of the state, 7 us here.  The sums over the
+// units before grow with their number: at 64 CSPAD frames (12,672 units) it is
+// 11 us against 14, and larger batches keep the three kernels.
+constexpr uint32_t kTailUnits = 16384, kTailUpf = 1024;
+
+bool tail_fits(uint64_t n_units, int32_t upf)
+{
+    return n_units > 0 && n_units <= kTailUnits && upf <= (int32_t)kTailUpf;
+}
+
+__global__ void __launch_bounds__(256) tail_kernel(TailArgs a)
+{
+    constexpr uint32_t NU = 4 * kScatterUnits;  // units of a workgroup
+    __shared__ uint32_t s_sum[4][2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t u0 = blockIdx.x * NU;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (last && a.stamp && tid == 0) a.state->t1 = wall_clock64();
+    const uint32_t f0 = u0 / a.upf, fs = f0 * a.upf;  // frame of unit u0, its first unit
+    // hits before unit u0, and before unit fs (all of a tail_fits batch's fit 32 bits)
+    uint32_t before = 0, before_f = 0;
+    for (uint32_t i = 4u * tid; i < u0; i += 4u * 256u) {
+        const uint4 c = *reinterpret_cast<const uint4 *>(a.unit_count + i);
+        before += c.x + c.y + c.z + c.w;
+        before_f += (i < fs ? c.x : 0u) + (i + 1u < fs ? c.y : 0u) + (i + 2u < fs ? c.z : 0u) + (i + 3u < fs ? c.w : 0u);
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+        before += (uint32_t)__shfl_xor((int)before, d, 64);
+        before_f += (uint32_t)__shfl_xor((int)before_f, d, 64);
+    }
+    if (lane == 0) {
+        s_sum[wave][0] = before;
+        s_sum[wave][1] = before_f;
+    }
+    __syncthreads();
+    before = before_f = 0;
+    for (int w = 0; w < 4; ++w) {
+        before += s_sum[w][0];
+        before_f += s_sum[w][1];
+    }
+    // lane l < 16 of every wave: unit u0 + l
+    const uint32_t unit = u0 + (uint32_t)lane;
+    const bool in = (uint32_t)lane < NU && unit < a.n_units;
+    uint32_t c = in ? a.unit_count[unit] : 0u;
+    const uint64_t base = in ? a.unit_base[unit] : kNoBase;
+    uint32_t incl = c;
+    for (int d = 1; d < (int)NU; d <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    const uint32_t at = before + incl - c;  // hits before the lane's unit
+    const uint32_t f = unit / a.upf, first = f * a.upf;
+    const uint32_t at_first = (uint32_t)__shfl((int)at, first >= u0 ? (int)(first - u0) & 63 : 0, 64);
+    if (wave == 0 && in) {
+        a.unit_local[unit] = at - (first >= u0 ? at_first : before_f);
+        if (unit == first) a.frame_offset[f] = at;
+        if (unit == a.n_units - 1u) {
+            a.frame_offset[a.n_frames] = at + c;
+            a.state->total = at + c;
+            publish_state(a.state, a.host);
+        }
+    }
+    // frames whose first unit is one of these
+    for (uint32_t g = (u0 + a.upf - 1u) / a.upf + (uint32_t)wave; g < a.n_frames && g * a.upf < u0 + NU; g += 4u) {
+        uint32_t n = 0;
+        unsigned long long ph = 0;
+        for (uint32_t i = (uint32_t)lane; i < a.upf; i += 64) {
+            n += a.unit_count[g * a.upf + i];
+            ph += a.unit_photons[g * a.upf + i];
+        }
+        for (int d = 1; d < 64; d <<= 1) {
+            n += (uint32_t)__shfl_xor((int)n, d, 64);
+            ph += __shfl_xor(ph, d, 64);
+        }
+        if (lane == 0) {
+            a.frame_hits[g] = n;
+            a.frame_photons[g] = ph;
+            if (a.host.frame_hits) {
+                a.host.frame_hits[g] = n;
+                a.host.frame_photons[g] = ph;
+                __threadfence_system();
+            }
+        }
+    }
+    if (base == kNoBase || (uint64_t)at + c > a.hits_cap) c = 0;
+    copy_runs(c, base, at, kScatterUnits * wave, lane, a.pool, a.hits);
+}
+
+hipError_t launch_tail(const TailArgs &a, hipStream_t s)
+{
+    if (!tail_fits(a.n_units, (int32_t)a.upf)) return hipErrorInvalidValue;
+    const uint32_t blocks = (a.n_units + 4 * kScatterUnits - 1) / (4 * kScatterUnits);
+    hipLaunchKernelGGL(tail_kernel, dim3(blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
