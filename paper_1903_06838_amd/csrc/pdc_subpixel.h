@@ -75,6 +75,7 @@ struct CaptureArgs {
     uint64_t n_frames;
     uint32_t upf;
     uint64_t frames_per_item;                  // set by the launch
+    uint32_t parts;                            // waves that share a unit's run (set by the launch)
     uint64_t n;
     float *patches;
     uint16_t *inputs;

@@ -961,14 +961,16 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
     __shared__ __align__(16) float s_p[kPatchWaves][kPatchHits * 25];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // item (strip, frame group) of the wave: blocks are dealt to the 8 chiplets
+    // item (strip, frame group, part) of the wave: blocks are dealt to the 8 chiplets
     // round-robin, and the chiplets take contiguous ranges of items
     const uint32_t nblk = gridDim.x, x = blockIdx.x & 7u;
     uint32_t before = 0;
     for (uint32_t y = 0; y < x; ++y) before += (nblk - y + 7u) >> 3;
-    const uint64_t item = (uint64_t)(before + (blockIdx.x >> 3)) * kPatchWaves + wv;
+    const uint64_t wid = (uint64_t)(before + (blockIdx.x >> 3)) * kPatchWaves + wv;
+    const uint64_t item = wid / a.parts;
+    const uint32_t part = (uint32_t)(wid - item * a.parts);
     const uint64_t ngrp = (a.n_frames + a.frames_per_item - 1) / a.frames_per_item;
-    if (item >= ngrp * a.upf) return;
+    if (item >= ngrp * (uint64_t)a.upf) return;
     const uint32_t strip = (uint32_t)(item / ngrp);
     const uint64_t f0 = (item - strip * ngrp) * a.frames_per_item;
     const uint64_t f1 = f0 + a.frames_per_item < a.n_frames ? f0 + a.frames_per_item : a.n_frames;
@@ -982,14 +984,17 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
         const uint32_t c_all = a.unit_count[unit];
         const uint64_t i0 = a.frame_offset[f] + a.unit_local[unit];
         const uint32_t cnt = i0 >= a.n ? 0u : (uint32_t)(a.n - i0 < c_all ? a.n - i0 : c_all);
-        for (uint32_t j0 = 0; j0 < cnt; j0 += kPatchHits) {
+        for (uint32_t j0 = part * kPatchHits; j0 < cnt; j0 += a.parts * kPatchHits) {
             const uint32_t nh = cnt - j0 < (uint32_t)kPatchHits ? cnt - j0 : (uint32_t)kPatchHits;
             float v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            uint32_t slow = 0;  // auto-ranging: columns not in range 0
+            int t = 0, r = 0, c = 0;  // tile, window row, first column of the window
             if (on && (uint32_t)hl < nh) {
                 const uint32_t p = a.hits[i0 + j0 + hl].x;
                 const uint32_t rt = p / (uint32_t)W;
-                const int c = (int)(p - rt * (uint32_t)W) - 2;  // first column of the window
-                const int t = (int)(rt / (uint32_t)H), r = (int)rt - t * H + wr - 2;
+                c = (int)(p - rt * (uint32_t)W) - 2;
+                t = (int)(rt / (uint32_t)H);
+                r = (int)rt - t * H + wr - 2;
                 const bool row_in = r >= 0 && r < H;
                 const uint64_t q = ((uint64_t)t * H + r) * (uint64_t)W + c;  // in the frame (used when inside)
                 const bool whole = c >= 0 && c + 4 < W;
@@ -1004,7 +1009,7 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
                         for (int e = 0; e < 5; ++e)
                             if (c + e >= 0 && c + e < W) v[e] = src[e];
                     }
-                } else if (row_in && whole && !a.src.gain_mode && B >= 4) {
+                } else if (row_in && whole && B >= 4) {
                     const Raw5 w = *reinterpret_cast<const Raw5 *>(a.src.frames + f * npix + q);
                     const Float5 pd = *reinterpret_cast<const Float5 *>(a.src.ped + q);
                     const Float5 kk = *reinterpret_cast<const Float5 *>(a.src.k + q);
@@ -1034,6 +1039,10 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
                         if (!meds) y = __fsub_rn(__fsub_rn(y, up ? hi[1] : lo[1]), up ? hi[2] : lo[2]);
                         v[e] = y;
                     }
+                    if (a.src.gain_mode) {
+#pragma unroll
+                        for (int e = 0; e < 5; ++e) slow |= w.w[e] >= 0x4000u ? 1u << e : 0u;
+                    }
                 } else if (row_in) {
 #pragma unroll
                     for (int e = 0; e < 5; ++e)
@@ -1043,6 +1052,11 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
             if (on) {
 #pragma unroll
                 for (int e = 0; e < 5; ++e) sp[hl * 25 + wr * 5 + e] = v[e];
+                while (slow) {
+                    const int e = __builtin_ctz(slow);
+                    slow &= slow - 1u;
+                    sp[hl * 25 + wr * 5 + e] = frames2_at(a.src, f, t, r, c + e);
+                }
             }
             wave_lds_wait();
             const uint64_t out0 = i0 + j0;
@@ -1069,7 +1083,9 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
 
 // Frames of an item: enough items for 32 waves a compute unit (8: 137 us, 16:
 // 114, 32: 100 at the size above), and where there are more a strip's frames
-// taken one after another.
+// taken one after another.  Batches of fewer units share each unit's run among
+// up to 16 waves (3 Jungfrau frames at occupancy 0.024, about 500 hits a
+// strip: 16 us; by a wave a unit, and a load a pixel for gain ranges, 158).
 hipError_t launch_capture(CaptureArgs a, uint32_t n_cu, hipStream_t s)
 {
     if (a.n == 0 || a.n_frames == 0 || a.upf == 0) return hipSuccess;
@@ -1077,7 +1093,9 @@ hipError_t launch_capture(CaptureArgs a, uint32_t n_cu, hipStream_t s)
     a.frames_per_item = units / want > 1 ? units / want : 1;
     if (a.frames_per_item > a.n_frames) a.frames_per_item = a.n_frames;
     const uint64_t items = (a.n_frames + a.frames_per_item - 1) / a.frames_per_item * a.upf;
-    const uint64_t blocks = (items + kPatchWaves - 1) / kPatchWaves;
+    const uint64_t parts = (want + units - 1) / units;
+    a.parts = (uint32_t)(parts < 1 ? 1 : (parts > 16 ? 16 : parts));
+    const uint64_t blocks = (items * a.parts + kPatchWaves - 1) / kPatchWaves;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     const auto k = a.corrected ? capture_kernel<true> : capture_kernel<false>;
     hipLaunchKernelGGL(k, dim3((uint32_t)blocks), dim3(64 * kPatchWaves), 0, s, a);

@@ -75,3 +75,36 @@ def test_windows(ctx, T, H, W, B, gm, flag):
         pdc.release_batch(ctx, b)
     finally:
         pdc.release_detector(ctx, det)
+
+
+@pytest.mark.parametrize("n", [500, 513, 1100])
+def test_many_units(n):
+    """Units around the number from which a unit is one wave's (8,192) and a
+    wave takes several frames (16 units a frame, one row a strip)."""
+    import os
+
+    import torch
+
+    from paper_1903_06838_amd import pdc
+
+    geom = synth.Geometry(1, 16, 24, 12)
+    ped, gain = synth.make_calibration(geom, 6)
+    raw = synth.make_frames(geom, ped, gain, n, 0.1, 6)
+    want = oracle_threads(raw, ped, gain, 12, keep_corrected=True)
+    exp = _cut(want["corrected"], want["hits"])
+    os.environ["PDC_STRIP_ROWS"] = "1"
+    try:
+        c = pdc.create(0)
+    finally:
+        del os.environ["PDC_STRIP_ROWS"]
+    try:
+        det = pdc.calibrate(c, pdc.geometry(1, 16, 24, 12), ped, gain, pdc.params(3.0, 5.0, 3.0, ADU, pdc.KEEP_MEDIANS))
+        b = pdc.process_frames(c, det, torch.from_numpy(raw).cuda(), n, raw.size)
+        out = torch.full((len(exp) + 1, 25), -1.0, dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        assert pdc.capture_patches(c, b, out, len(exp) + 1) == len(exp)
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:-1].view(np.uint32), exp.view(np.uint32)) and np.all(got[-1] == -1.0)
+        pdc.release_batch(c, b)
+    finally:
+        pdc.destroy(c)
