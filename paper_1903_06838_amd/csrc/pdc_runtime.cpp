@@ -74,7 +74,7 @@ struct Detector {
     bool release_requested = false;
 };
 
-constexpr uint64_t kFmtChunk = 65536, kFmtSlots = 4;  // records of a chunk, chunks in flight to the host
+constexpr uint64_t kFmtChunk = 16384, kFmtSlots = 4;  // records of a chunk, chunks in flight to the host
 constexpr uint64_t kMirrorFrames = 65536;  // frames whose counts the kernels also write to pinned memory
 
 // Device buffers of one batch; kept by the context and reused.
