@@ -278,8 +278,8 @@ pdc_status pdc_autotune(pdc_ctx *ctx, int32_t det, const uint16_t *frames_dev, u
  * be NULL) the frame-kernel times, row r of 3 for the r-th strip height,
  * *n_tried (may be NULL) the strip heights timed.  ESTATE while the detector
  * has outstanding batches or graphs (they hold its strip plan), does not
- * take the persistent kernel, or has an odd bank width or (single gain) cols
- * % 4 != 0.  Synchronous; runs 9 batches per height. */
+ * take the persistent kernel, or has banks of an odd width or wider than 256
+ * columns or (single gain) cols % 4 != 0.  Synchronous; runs 9 batches per height. */
 pdc_status pdc_autotune_strips(pdc_ctx *ctx, int32_t det, const uint16_t *frames_dev, uint64_t n_frames,
                                uint64_t hit_capacity, void *hip_stream, int32_t *rows_out, int32_t *mult_out,
                                float *ms_out, int32_t *n_tried);

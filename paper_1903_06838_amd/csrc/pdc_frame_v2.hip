@@ -556,8 +556,9 @@ constexpr int kV2Finish = L == 4 ? 4 : (L == 8 ? 3 : 2);
 // Bank-rows a lane group takes one after another in a frame: 256-column banks
 // need 16 lanes for four waves per SIMD (128 registers), and two passes keep
 // their strips as high as the others' (a strip loads two halo rows).
-template <int L>
-constexpr int kV2Passes = L == 16 ? 2 : 1;
+// (Banks of 257 to 512 columns: 32 columns a lane, one pass, half the waves.)
+template <int L, int Q>
+constexpr int kV2Passes = L == 16 && Q == 2 ? 2 : 1;
 
 // The launch's arguments, read from the argument memory (scalar loads, cached).
 // fresh() makes the fields read through it come from there at that place: read
@@ -577,7 +578,7 @@ __device__ __forceinline__ V2ArgsK fresh(V2ArgsK a)
 template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
 __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
 {
-    constexpr int V = 8 * Q + R, G = 64 / L, S = kV2Finish<L>, P = kV2Passes<L>;
+    constexpr int V = 8 * Q + R, G = 64 / L, S = kV2Finish<L>, P = kV2Passes<L, Q>;
     constexpr int kCntRegs = (kV2Threads / L * P + 63) / 64;  // bank-rows of a workgroup, 64 a register
     constexpr int kBitWords = (8 * L * Q + L * R + 31) / 32;  // of the widest bank of this layout
     static_assert(V <= 32, "a lane's values are bits of one mask");
@@ -1238,6 +1239,14 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
     frame_body<L, Q, R, KEEP, CMM, MG, ODD>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
 }
 
+// Banks of 257 to 512 columns: 32 values a lane, with dark and 1/gain and the next
+// words 130 registers, so one workgroup (two waves per SIMD) a compute unit.
+template <bool KEEP>
+__global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(2, 2))) frame_kernel_v2_wide(V2Args)
+{
+    frame_body<16, 4, 0, KEEP, 0, false>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
+}
+
 // Several detectors' batches in one launch: the work items of detector d are
 // [first[d], first[d + 1]) of the launch (finer frame groups than a launch
 // of its own, so that items of unequal cost even out as they are handed
@@ -1276,11 +1285,12 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
 // frame's words have to fit four waves per SIMD (128 registers).
 int v2_layout_of(int B)
 {
-    return B <= 64 ? 0 : (B <= 96 ? 1 : (B <= 128 ? 2 : (B <= 200 ? 3 : (B <= 256 ? 4 : -1))));
+    return B <= 64 ? 0 : (B <= 96 ? 1 : (B <= 128 ? 2 : (B <= 200 ? 3 : (B <= 256 ? 4 : (B <= 512 ? 5 : -1)))));
 }
 int v2_layout_bank_rows(int layout)
 {
-    return layout < 2 ? kV2Threads / 4 : (layout < 4 ? kV2Threads / 8 : kV2Threads / 16 * kV2Passes<16>);
+    return layout < 2 ? kV2Threads / 4
+                      : (layout < 4 ? kV2Threads / 8 : kV2Threads / 16 * (layout == 4 ? kV2Passes<16, 2> : 1));
 }
 
 size_t v2_layout_finish_bytes(int layout)
@@ -1327,6 +1337,14 @@ hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bo
 {
     const int lay = v2_layout_of(a.B);
     if (a.B < 1 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return hipErrorInvalidValue;
+    if (lay == 5) {
+        if ((a.B & 1) || a.cm_mode || a.gain_mode) return hipErrorInvalidValue;
+        auto k = keep ? frame_kernel_v2_wide<true> : frame_kernel_v2_wide<false>;
+        hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(kV2Threads), lds, s, a);
+        return hipGetLastError();
+    }
     switch (lay) {
     case 0: return launch_v2_t<4, 2, 0>(a, grid, lds, keep, s);
     case 1: return launch_v2_t<4, 3, 0>(a, grid, lds, keep, s);
@@ -1339,7 +1357,7 @@ hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bo
 int v2_mix_variant(const V2Args &a, bool keep)
 {
     const int lay = v2_layout_of(a.B);
-    if (keep || a.cm_mode || a.meds || a.B < 1 || (a.B & 1) || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return -1;
+    if (keep || a.cm_mode || a.meds || a.B < 1 || (a.B & 1) || lay == 5 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return -1;
     return lay + (a.gain_mode ? 5 : 0);
 }
 

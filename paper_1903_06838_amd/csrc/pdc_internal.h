@@ -129,6 +129,8 @@ constexpr int kBankShift = 20;
 // workgroup holds with it and the bytes of its medians' finish scratch, which
 // lies in a hit list.
 int v2_layout_of(int B);
+// Workgroups a compute unit holds at once.
+inline int v2_groups_per_cu(int B) { return B > 256 ? 1 : kV2GroupsPerCu; }
 int v2_layout_bank_rows(int layout);
 size_t v2_layout_finish_bytes(int layout);
 size_t frame_kernel_v2_lds_bytes(int rmax, int W, int B, int nb, int seed_cap, int hit_cap);

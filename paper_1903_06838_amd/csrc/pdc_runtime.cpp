@@ -365,23 +365,26 @@ bool plan_v1(Detector &d)
 
 // Plan of the persistent kernel: strips of at most rmax loaded rows, as many
 // strips x frame groups as there are compute units; false if the geometry is
-// outside its fast path (one-column banks or banks wider than 256, odd widths
-// with gain ranges or a thresholded mean, or too little LDS).  Odd widths have
-// a compiled body for the median alone: 64 frames of 8 x 185 x 194 pixels in
-// banks of 97 take it 68 us, the general kernel 624 us.
+// outside its fast path (one-column banks, banks wider than 512 or, where odd,
+// 256, odd widths and widths over 256 with gain ranges or a thresholded mean,
+// or too little LDS).  Odd widths and widths over 256 have compiled bodies for
+// the median alone: 64 frames of 8 x 185 x 194 pixels in banks of 97 take
+// theirs 68 us and the general kernel 624 us, 64 frames of 512 x 1024 in banks
+// of 512 the whole call 122 us and 2,437 us.
 bool plan_v2(pdc_ctx *ctx, Detector &d)
 {
     const pdc_geometry &g = d.g;
     d.v2_ok = false;
-    if (g.bank_cols > 256 || g.bank_cols < 2) return false;
-    if ((g.bank_cols & 1) && (g.gain_mode || d.p.cm_mode != PDC_CM_MEDIAN)) return false;
+    if (g.bank_cols > 512 || g.bank_cols < 2) return false;
+    if (((g.bank_cols & 1) || g.bank_cols > 256) && (g.gain_mode || d.p.cm_mode != PDC_CM_MEDIAN)) return false;
+    if ((g.bank_cols & 1) && g.bank_cols > 256) return false;
     const int nb = g.cols / g.bank_cols;
     const int layout = v2_layout_of(g.bank_cols);
     const int max_bank_rows = v2_layout_bank_rows(layout);
     int rmax_lim = max_bank_rows / nb;
     // room in LDS for seeds on a twelfth of the strip's pixels at least (1024-
     // column detectors: 15 rows rather than 16)
-    const size_t lds_wg = (size_t)ctx->max_lds / kV2GroupsPerCu;
+    const size_t lds_wg = (size_t)ctx->max_lds / v2_groups_per_cu(g.bank_cols);
 #ifdef PDC_PHASE_TIMERS
     const size_t static_lds = 2048;  // the tracing build's per-wave counters
 #else
@@ -454,7 +457,7 @@ bool plan_v2(pdc_ctx *ctx, Detector &d)
         const int sw = (int)next_pow2(g.bank_cols);
         for (int srt = own_rows_max + 2; srt >= 1 && !d.fb_ok; --srt) {
             const size_t lds = frame_kernel_v1_lds_bytes(own_rows_max, g.cols, nb, sw, srt, d.v2_max_unit_hits);
-            if (lds <= lds_cap) {
+            if (lds + 512 <= (size_t)ctx->max_lds) {
                 d.fb_ok = true;
                 d.fb_strip_rows = own_rows_max;
                 d.fb_sort_rows = srt;
@@ -922,7 +925,7 @@ void set_path(const Detector &d, Batch &bt, int path)
 {
     bt.path = path;
     if (path == 2) {
-        const int fgb = frame_groups(d.n_cu * kV2GroupsPerCu, d.n_strips, bt.n_frames, d.fg_mult * bt.fg_more);
+        const int fgb = frame_groups(d.n_cu * v2_groups_per_cu(d.g.bank_cols), d.n_strips, bt.n_frames, d.fg_mult * bt.fg_more);
         const uint64_t fg = (uint64_t)std::max(1.0, std::floor((double)fgb * bt.share));
         bt.n_fg = (int)std::max<uint64_t>(1, std::min<uint64_t>(fg, bt.n_frames));
         bt.upf = d.n_strips;
@@ -2423,8 +2426,9 @@ pdc_status pdc_autotune_strips(pdc_ctx *ctx, int32_t det, const uint16_t *frames
         return fail(ctx, PDC_ESTATE, "unknown detector %d", det);
     if (n_frames < 1 || !frames_dev) return fail(ctx, PDC_EINVAL, "need frames_dev and n_frames >= 1");
     Detector &d = ctx->dets[det];
-    // (widths off the persistent kernel's 4-column grid keep their one strip height)
-    if (!d.v2_ok || (d.g.bank_cols & 1) || (!d.g.gain_mode && d.g.cols % 4))
+    // (widths off the persistent kernel's 4-column grid and banks wider than 256
+    // keep their one strip height)
+    if (!d.v2_ok || (d.g.bank_cols & 1) || d.g.bank_cols > 256 || (!d.g.gain_mode && d.g.cols % 4))
         return fail(ctx, PDC_ESTATE, "the detector does not take the tuned forms of the persistent kernel");
     if (d.pending) return fail(ctx, PDC_ESTATE, "the detector has outstanding batches or graphs");
     HIP_TRY(ctx, hipSetDevice(ctx->device));

@@ -1,5 +1,5 @@
-"""The persistent kernel on widths off its 4-column grid, bit for bit against the
-oracles: banks of an odd width (the last column of each has no partner, and
+"""The persistent kernel on widths off its 4-column grid, and on banks wider than
+256 columns, bit for bit against the oracles: banks of an odd width (the last column of each has no partner, and
 banks and rows start at odd columns and addresses) around every lane layout's
 capacity, rows of an even width that is no multiple of 4, with and without
 Frames2, one frame and several, at the buffer's last pixel, and where a strip's
@@ -82,3 +82,30 @@ def test_odd_banks_mean(cm_mode):
         got, path = _process(raw, ped, gain, B, True, cm_mode, 2)
         assert path in paths
         assert_same(got, want, corrected=True)
+
+
+@pytest.mark.parametrize("B,nb", [(258, 1), (258, 2), (300, 3), (384, 1), (510, 4), (512, 1), (512, 2), (512, 4),
+                                  (257, 1), (511, 2), (514, 1)])
+@pytest.mark.parametrize("n,keep", [(1, True), (5, True), (6, False)])
+def test_wide_banks(B, nb, n, keep):
+    """Even widths up to 512 take the persistent kernel, the others the general one."""
+    geom = synth.Geometry(2, 33, B * nb, B)
+    ped, gain = synth.make_calibration(geom, 700 + B)
+    raw = synth.make_frames(geom, ped, gain, n, 0.03, 700 + B)
+    want = oracle_threads(raw, ped, gain, B, keep_corrected=keep)
+    got, path = _process(raw, ped, gain, B, keep)
+    assert path in ((2, 3) if B % 2 == 0 and B <= 512 else (1,))
+    assert_same(got, want, corrected=keep)
+
+
+def test_wide_banks_flood():
+    geom = synth.Geometry(1, 40, 1024, 512)
+    ped = np.full(geom.shape, 1000.0, np.float32)
+    gain = np.ones(geom.shape, np.float32)
+    raw = np.full((3, *geom.shape), 1000, np.uint16)
+    for k in range(4):
+        raw[1, 0, :12, k::9] = 1200
+    want = oracle_threads(raw, ped, gain, 512, keep_corrected=True)
+    got, path = _process(raw, ped, gain, 512, True)
+    assert path in (2, 3)
+    assert_same(got, want, corrected=True)
