@@ -45,6 +45,17 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
+// Four values as bf16 to base[0], base[S], base[2 S], base[3 S].
+template <int S>
+__device__ __forceinline__ void put4(uint16_t *base, float a, float b, float c, float d)
+{
+    const uint32_t lo = pk_bf16(a, b), hi = pk_bf16(c, d);
+    base[0] = (uint16_t)lo;
+    base[S] = (uint16_t)(lo >> 16);
+    base[2 * S] = (uint16_t)hi;
+    base[3 * S] = (uint16_t)(hi >> 16);
+}
+
 // Operand fragment: 8 bf16 values base[o * SO + (k + j) * SK], j = 0..7.
 // With SK == 1 one 16-byte load (o * SO + k is a multiple of 8 at every call).
 template <int SO, int SK>
@@ -259,7 +270,14 @@ __device__ __forceinline__ void stage_weights(WeightLds &W, const float *theta, 
 {
     const u32x4 *src = reinterpret_cast<const u32x4 *>(packed);
     u32x4 *dst = reinterpret_cast<u32x4 *>(W.w);
-    for (int i = threadIdx.x; i < kPackElems / 8; i += blockDim.x) dst[i] = src[i];
+    // (all of a thread's loads at once: one by one each waited for its own)
+    constexpr int N = kPackElems / 8, T = 64 * kWaves, K = (N + T - 1) / T;
+    u32x4 w[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) w[k] = src[(int)threadIdx.x + k * T < N ? (int)threadIdx.x + k * T : N - 1];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if ((int)threadIdx.x + k * T < N) dst[threadIdx.x + k * T] = w[k];
     for (int i = threadIdx.x; i < 64; i += blockDim.x) {
         W.b1[i] = theta[kOffB1 + i];
         W.b2[i] = theta[kOffB2 + i];
@@ -267,24 +285,35 @@ __device__ __forceinline__ void stage_weights(WeightLds &W, const float *theta, 
     if (threadIdx.x < 4) W.b3[threadIdx.x] = threadIdx.x < 2 ? theta[kOffB3 + threadIdx.x] : 0.0f;
 }
 
-// Forward pass of the tile of hits [h0, h0 + 32): X, H1, H2 in LDS (bf16),
-// ReLU activity bits pos1/pos2 (bit i of [rt][nt] for C-layout row i), and
-// the outputs y[rt] in C layout (columns 0 and 1 valid).  Rows past n hold
-// zero inputs.
-__device__ __forceinline__ void tile_forward(const float *patches, uint64_t n, uint64_t h0, float inv_adu,
-                                             const WeightLds &W, FwdLds &F, int lane, f32x4 (&y)[2],
-                                             uint32_t (&pos1)[2][4], uint32_t (&pos2)[2][4])
+// A tile's words of one lane, element lane + 64 j of [32][32] in x[j]: the
+// padding columns 25..31 and rows past n are zeros (and written as such: LDS
+// left over from earlier kernels may hold bit patterns that read as bf16 inf or
+// NaN, and inf * 0 is NaN).
+__device__ __forceinline__ void tile_load(const float *patches, uint64_t n, uint64_t h0, int lane,
+                                          float (&x)[kTile * 32 / 64])
 {
-    const uint64_t nv = n - h0 < (uint64_t)kTile ? n - h0 : (uint64_t)kTile;
+    const uint64_t nv = h0 >= n ? 0 : (n - h0 < (uint64_t)kTile ? n - h0 : (uint64_t)kTile);
     const float *src = patches + h0 * 25;
-    // every element of the tile is written, the padding columns 25..31 and
-    // rows past n as zeros: LDS left over from earlier kernels may hold
-    // bit patterns that read as bf16 inf or NaN, and inf * 0 is NaN
-    for (int e = lane; e < kTile * 32; e += 64) {
-        const int r = e >> 5, k = e & 31;
-        const float v = (k < 25 && (uint64_t)r < nv) ? src[r * 25 + k] * inv_adu : 0.0f;
-        F.X[e] = f2bf(v);
+    if (nv == 0) return;  // (uniform) past the last tile
+    const int k = lane & 31, kc = k < 25 ? k : 24;
+#pragma unroll
+    for (int j = 0; j < kTile * 32 / 64; ++j) {
+        const int r = (lane + 64 * j) >> 5, last = (int)nv - 1;
+        const float v = src[(r < last ? r : last) * 25 + kc];
+        x[j] = k < 25 && r <= last ? v : 0.0f;
     }
+}
+
+// Forward pass of a tile of 32 hits from its loaded words: X, H1, H2 in LDS
+// (bf16), ReLU activity bits pos1/pos2 (bit i of [rt][nt] for C-layout row i),
+// and the outputs y[rt] in C layout (columns 0 and 1 valid).
+__device__ __forceinline__ void tile_forward(const float (&x)[kTile * 32 / 64], float inv_adu, const WeightLds &W,
+                                             FwdLds &F, int lane, f32x4 (&y)[2], uint32_t (&pos1)[2][4],
+                                             uint32_t (&pos2)[2][4])
+{
+#pragma unroll
+    for (int j = 0; j < kTile * 32 / 64; j += 4)
+        put4<64>(F.X + lane + 64 * j, x[j] * inv_adu, x[j + 1] * inv_adu, x[j + 2] * inv_adu, x[j + 3] * inv_adu);
     wave_lds_sync();
     const int lo = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
     // layer 1: X[32 x 32] W1[32 x 64]
@@ -297,12 +326,14 @@ __device__ __forceinline__ void tile_forward(const float *patches, uint64_t n, u
             const int col = 16 * nt + lo;
             const float bias = W.b1[col];
             uint32_t pm = 0;
+            float z[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float z = acc[i] + bias;
-                F.H1[(16 * rt + rq + i) * 64 + col] = f2bf(z > 0.0f ? z : 0.0f);
-                pm |= (uint32_t)(z > 0.0f) << i;
+                z[i] = acc[i] + bias;
+                pm |= (uint32_t)(z[i] > 0.0f) << i;
+                z[i] = z[i] > 0.0f ? z[i] : 0.0f;
             }
+            put4<64>(F.H1 + (16 * rt + rq) * 64 + col, z[0], z[1], z[2], z[3]);
             pos1[rt][nt] = pm;
         }
     }
@@ -319,12 +350,14 @@ __device__ __forceinline__ void tile_forward(const float *patches, uint64_t n, u
             const int col = 16 * nt + lo;
             const float bias = W.b2[col];
             uint32_t pm = 0;
+            float z[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float z = acc[i] + bias;
-                F.H2[(16 * rt + rq + i) * 64 + col] = f2bf(z > 0.0f ? z : 0.0f);
-                pm |= (uint32_t)(z > 0.0f) << i;
+                z[i] = acc[i] + bias;
+                pm |= (uint32_t)(z[i] > 0.0f) << i;
+                z[i] = z[i] > 0.0f ? z[i] : 0.0f;
             }
+            put4<64>(F.H2 + (16 * rt + rq) * 64 + col, z[0], z[1], z[2], z[3]);
             pos2[rt][nt] = pm;
         }
     }
@@ -646,6 +679,11 @@ __device__ __forceinline__ float col_sum(float v)
     return v;
 }
 
+// (A batch of 2,048 hits is one tile a wave, so the kernel is one wave's chain of
+// instructions and waits: all its global loads are issued before the weights
+// are staged and bf16 values are made in pairs, 16.4 -> 13.9 us a step; with
+// the update's sums loaded 32 slots ahead, 4.9 -> 4.2, eight steps and the
+// read-back take 208 us where they took 238.)
 // Per-wave gradient of L = sum((y - t)^2) / (2 n) over its tiles, written to
 // the wave's slot (kMlpSlotStride floats: parameters in packed order, then
 // sum((y - t)^2)).  Products take bf16 operands (X, H1, H2, dY, dH2, dH1 and
@@ -657,14 +695,30 @@ __global__ void __launch_bounds__(256) mlp_grad_kernel(const float *patches, con
     __shared__ WeightLds W;
     __shared__ FwdLds Fs[kWaves];
     __shared__ BwdLds Bs[kWaves];
-    stage_weights(W, theta, packed);
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     FwdLds &F = Fs[wv];
     BwdLds &Bk = Bs[wv];
+    const int lo = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
+    const uint64_t tiles = (n + kTile - 1) / kTile;
+    // a tile's patches and targets are loaded before the weights (the first)
+    // or during the tile before, all at once
+    float x[kTile * 32 / 64], tg[2][4];
+    auto load = [&](uint64_t t) {
+        tile_load(patches, n, t * kTile, lane, x);
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t h = t * kTile + 16 * rt + rq + i;
+                tg[rt][i] = target[2 * (h < n ? h : n - 1) + (lo & 1)];
+            }
+    };
+    uint64_t t = (uint64_t)blockIdx.x * kWaves + wv;
+    load(t);
+    stage_weights(W, theta, packed);
     for (int i = lane; i < kTile * 32; i += 64) Bk.DY[i] = 0;
     __syncthreads();
-    const int lo = lane & 15, kq = 8 * (lane >> 4), rq = 4 * (lane >> 4);
 
     f32x4 gW1[2][4], gW2[4][4], gW3[4];
 #pragma unroll
@@ -679,28 +733,26 @@ __global__ void __launch_bounds__(256) mlp_grad_kernel(const float *patches, con
         for (int b = 0; b < 4; ++b) gW1[a][b] = zero4();
     float gb1[4] = {0.f, 0.f, 0.f, 0.f}, gb2[4] = {0.f, 0.f, 0.f, 0.f}, gb3 = 0.f, lsum = 0.f;
 
-    const uint64_t tiles = (n + kTile - 1) / kTile;
-    for (uint64_t t = (uint64_t)blockIdx.x * kWaves + wv; t < tiles; t += (uint64_t)gridDim.x * kWaves) {
+    for (; t < tiles; t += (uint64_t)gridDim.x * kWaves) {
         const uint64_t h0 = t * kTile;
         f32x4 y[2];
         uint32_t p1[2][4], p2[2][4];
-        tile_forward(patches, n, h0, inv_adu, W, F, lane, y, p1, p2);
+        tile_forward(x, inv_adu, W, F, lane, y, p1, p2);
         // dY = (y - t) / n, zero for columns >= 2 and rows past n
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+        for (int rt = 0; rt < 2; ++rt) {
+            float d[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int row = 16 * rt + rq + i;
-                const uint64_t h = h0 + row;
-                float d = 0.0f;
-                if (lo < 2 && h < n) {
-                    const float e = y[rt][i] - target[2 * h + lo];
-                    lsum += e * e;
-                    d = e * inv_n;
-                }
-                gb3 += d;
-                Bk.DY[row * 32 + lo] = f2bf(d);
+                const bool in = lo < 2 && h0 + (uint64_t)(16 * rt + rq + i) < n;
+                const float e = in ? y[rt][i] - tg[rt][i] : 0.0f;
+                lsum += e * e;
+                d[i] = e * inv_n;
+                gb3 += d[i];
             }
+            put4<32>(Bk.DY + (16 * rt + rq) * 32 + lo, d[0], d[1], d[2], d[3]);
+        }
+        load(t + (uint64_t)gridDim.x * kWaves);
         wave_lds_sync();
         // dW3[64 x 16] += H2^T[64 x 32] dY[32 x 16]
 #pragma unroll
@@ -714,12 +766,13 @@ __global__ void __launch_bounds__(256) mlp_grad_kernel(const float *patches, con
             for (int nt = 0; nt < 4; ++nt) {
                 const f32x4 acc = mfma(a, frag<32, 1>(W.w + kPackW3p, 16 * nt + lo, kq), zero4());
                 const int col = 16 * nt + lo;
+                float g[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float g = ((p2[rt][nt] >> i) & 1u) ? acc[i] : 0.0f;
-                    gb2[nt] += g;
-                    Bk.D[(16 * rt + rq + i) * 64 + col] = f2bf(g);
+                    g[i] = ((p2[rt][nt] >> i) & 1u) ? acc[i] : 0.0f;
+                    gb2[nt] += g[i];
                 }
+                put4<64>(Bk.D + (16 * rt + rq) * 64 + col, g[0], g[1], g[2], g[3]);
             }
         }
         wave_lds_sync();
@@ -740,12 +793,13 @@ __global__ void __launch_bounds__(256) mlp_grad_kernel(const float *patches, con
                 f32x4 acc = mfma(a0, frag<64, 1>(W.w + kPackW2, 16 * nt + lo, kq), zero4());
                 acc = mfma(a1, frag<64, 1>(W.w + kPackW2, 16 * nt + lo, 32 + kq), acc);
                 const int col = 16 * nt + lo;
+                float g[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float g = ((p1[rt][nt] >> i) & 1u) ? acc[i] : 0.0f;
-                    gb1[nt] += g;
-                    F.H2[(16 * rt + rq + i) * 64 + col] = f2bf(g);
+                    g[i] = ((p1[rt][nt] >> i) & 1u) ? acc[i] : 0.0f;
+                    gb1[nt] += g[i];
                 }
+                put4<64>(F.H2 + (16 * rt + rq) * 64 + col, g[0], g[1], g[2], g[3]);
             }
         }
         wave_lds_sync();
@@ -833,7 +887,7 @@ hipError_t launch_mlp_grad(const float *patches, const float *target, uint64_t n
 // __fsqrt_rn is not used: it maps to the native approximation.
 // One training step's update after mlp_grad_kernel, in one kernel: each
 // parameter's gradient summed over the slots in index order (the additions
-// of slot_reduce_kernel, with the loads issued eight ahead), then Adam as
+// of slot_reduce_kernel, with the loads issued 32 ahead), then Adam as
 // above, then the bf16 copies of the new value in every packed layout
 // (the packing's zero padding is never written).  grad also receives the
 // sums (the loss term at kMlpParams).
@@ -845,12 +899,12 @@ __global__ void mlp_update_kernel(const float *slots, uint32_t n_slots, float *g
     if (p > kMlpParams) return;
     float s = 0.0f;
     uint32_t i = 0;
-    for (; i + 8 <= n_slots; i += 8) {
-        float t[8];
+    for (; i + 32 <= n_slots; i += 32) {
+        float t[32];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t[j] = slots[(uint64_t)(i + j) * kMlpSlotStride + p];
+        for (int j = 0; j < 32; ++j) t[j] = slots[(uint64_t)(i + j) * kMlpSlotStride + p];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) s += t[j];
+        for (int j = 0; j < 32; ++j) s += t[j];
     }
     for (; i < n_slots; ++i) s += slots[(uint64_t)i * kMlpSlotStride + p];
     grad[p] = s;
