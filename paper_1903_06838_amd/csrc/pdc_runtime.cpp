@@ -76,6 +76,7 @@ struct Detector {
 
 constexpr uint64_t kFmtChunk = 16384, kFmtSlots = 4;  // records of a chunk, chunks in flight to the host
 constexpr uint64_t kMirrorFrames = 65536;  // frames whose counts the kernels also write to pinned memory
+constexpr uint64_t kMirrorInline = 4096;   // of them in the allocation of the state
 
 // Device buffers of one batch; kept by the context and reused.
 struct Buffers {
@@ -103,6 +104,7 @@ struct Buffers {
     uint32_t *host_hits = nullptr;     // pinned [cap_host]: frame_hits, then frame_photons
     unsigned long long *host_photons = nullptr;
     uint64_t cap_host = 0;
+    void *host_more = nullptr;         // their memory beyond kMirrorInline frames
     hipEvent_t ev_start = nullptr, ev_end = nullptr;  // around the batch's work on its stream
     hipEvent_t ev_use = nullptr;    // after summary work on a caller's stream
     bool used = false;              // ev_use recorded since the batch was launched
@@ -153,7 +155,7 @@ void free_buffers(Buffers *b)
     hipFree(b->fb_units);
     hipFree(b->state);
     if (b->host_state) hipHostFree(b->host_state);
-    if (b->host_photons) hipHostFree(b->host_photons);
+    if (b->host_more) hipHostFree(b->host_more);
     if (b->ev_start) hipEventDestroy(b->ev_start);
     if (b->ev_end) hipEventDestroy(b->ev_end);
     if (b->ev_use) hipEventDestroy(b->ev_use);
@@ -179,7 +181,6 @@ struct pdc_ctx {
     uint64_t next_batch = 1;
     std::string err;
     HitRecord *fmt_buf = nullptr;  // pinned staging of host-destination get_hits: kFmtSlots chunks
-    uint64_t fmt_cap = 0;
     hipEvent_t fmt_done[kFmtSlots] = {};
     bool force_v1 = false;         // PDC_FORCE_GENERAL=1 in the environment
     int strip_rows = 0;            // PDC_STRIP_ROWS=n: own rows per strip at most n for new detectors
@@ -496,7 +497,12 @@ pdc_status ensure_buffers(pdc_ctx *ctx, Buffers *b, uint64_t n_units, uint64_t n
 {
     if (!b->state) {
         HIP_TRY(ctx, hipMalloc((void **)&b->state, sizeof(BatchState)));
-        HIP_TRY(ctx, hipHostMalloc((void **)&b->host_state, sizeof(BatchState), hipHostMallocCoherent));
+        // the state, then the counts of up to kMirrorInline frames
+        constexpr uint64_t at = (sizeof(BatchState) + 63) / 64 * 64, per = sizeof(unsigned long long) + sizeof(uint32_t);
+        HIP_TRY(ctx, hipHostMalloc((void **)&b->host_state, at + kMirrorInline * per, hipHostMallocCoherent));
+        b->host_photons = reinterpret_cast<unsigned long long *>(reinterpret_cast<unsigned char *>(b->host_state) + at);
+        b->host_hits = reinterpret_cast<uint32_t *>(b->host_photons + kMirrorInline);
+        b->cap_host = kMirrorInline;
         HIP_TRY(ctx, hipEventCreate(&b->ev_start));
         HIP_TRY(ctx, hipEventCreate(&b->ev_end));
         HIP_TRY(ctx, hipEventCreateWithFlags(&b->ev_use, hipEventDisableTiming));
@@ -518,12 +524,14 @@ pdc_status ensure_buffers(pdc_ctx *ctx, Buffers *b, uint64_t n_units, uint64_t n
     }
     const uint64_t host = std::min(n_frames, kMirrorFrames);
     if (host > b->cap_host) {
-        if (b->host_photons) hipHostFree(b->host_photons);
+        if (b->host_more) hipHostFree(b->host_more);
+        b->host_more = nullptr;
         b->host_photons = nullptr;
         b->host_hits = nullptr;
         b->cap_host = 0;
-        HIP_TRY(ctx, hipHostMalloc((void **)&b->host_photons,
-                                   host * (sizeof(unsigned long long) + sizeof(uint32_t)), hipHostMallocCoherent));
+        HIP_TRY(ctx, hipHostMalloc(&b->host_more, host * (sizeof(unsigned long long) + sizeof(uint32_t)),
+                                   hipHostMallocCoherent));
+        b->host_photons = static_cast<unsigned long long *>(b->host_more);
         b->host_hits = reinterpret_cast<uint32_t *>(b->host_photons + host);
         b->cap_host = host;
     }
@@ -1165,6 +1173,16 @@ pdc_status pdc_create(int32_t device, pdc_ctx **out)
                 g_scratch_ptr[device] = static_cast<unsigned char *>(p);
         }
     }
+    // (here and not at the first call that needs it: pinning takes longer than a
+    // small batch)
+    bool pinned = hipHostMalloc((void **)&ctx->fmt_buf, kFmtSlots * kFmtChunk * sizeof(HitRecord), hipHostMallocCoherent) ==
+                  hipSuccess;
+    for (hipEvent_t &e : ctx->fmt_done)
+        pinned = pinned && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!pinned) {
+        pdc_destroy(ctx);
+        return fail(nullptr, PDC_ENOMEM, "pinned staging allocation failed");
+    }
     *out = ctx;
     return PDC_OK;
 }
@@ -1506,16 +1524,7 @@ pdc_status pdc_get_hits(pdc_ctx *ctx, uint64_t batch, pdc_hit *dst, uint64_t dst
             // per slot, while the host copies the slots before it out (16 CSPAD
             // frames' 370,000 records through a device buffer and pageable
             // copies: 439 us the call, 341 us so)
-            const uint64_t chunk = std::min(kFmtChunk, n_out), slots = std::min((n_out + chunk - 1) / chunk, kFmtSlots);
-            if (chunk * slots > ctx->fmt_cap) {
-                if (ctx->fmt_buf) hipHostFree(ctx->fmt_buf);
-                ctx->fmt_buf = nullptr;
-                ctx->fmt_cap = 0;
-                HIP_TRY(ctx, hipHostMalloc((void **)&ctx->fmt_buf, chunk * slots * sizeof(HitRecord), hipHostMallocCoherent));
-                ctx->fmt_cap = chunk * slots;
-            }
-            for (hipEvent_t &e : ctx->fmt_done)
-                if (!e) HIP_TRY(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            constexpr uint64_t chunk = kFmtChunk, slots = kFmtSlots;
             const uint64_t n_chunks = (n_out + chunk - 1) / chunk;
             for (uint64_t k = 0, sent = 0; k < n_chunks; ++k) {
                 for (; sent < n_chunks && sent < k + slots; ++sent) {
