@@ -745,12 +745,13 @@ def main():
         launches = args.steps + args.warmup
         names = ["A", "bar_AB", "medians", "seeds", "local_max", "hit_writes", "bar_BA"]
         rows = [[phase_buf[w * 8 + p] / (launches * N * n_strips) for p in range(7)] for w in range(16)]
+        rows = [r for r in rows if any(r)]  # waves of a workgroup
         log("phase cycles per strip-frame per wave (s_memtime), %d launches of %d frames, %d strips:" % (
             launches, N, n_strips))
         log("wave " + " ".join("%10s" % n for n in names) + "      total")
         for w, r in enumerate(rows):
             log("%4d " % w + " ".join("%10.0f" % x for x in r) + " %10.0f" % sum(r))
-        mean = [sum(r[p] for r in rows) / 16 for p in range(7)]
+        mean = [sum(r[p] for r in rows) / max(1, len(rows)) for p in range(7)]
         log("mean " + " ".join("%10.0f" % x for x in mean) + " %10.0f" % sum(mean))
         print(json.dumps({"phase_timers": True, "frame_kernel_ms": sum(mains) / len(mains), "phases": names,
                           "cycles_per_strip_frame_per_wave": [[round(x, 1) for x in r] for r in rows]}))

@@ -184,9 +184,9 @@ hipError_t launch_frame_kernel_v1(const FrameKernelArgs &a, uint32_t grid, size_
 hipError_t launch_frame_sums(const uint32_t *unit_count, const unsigned long long *unit_photons,
                              uint64_t n_frames, int32_t units_per_frame, uint32_t *unit_local,
                              uint32_t *frame_hits, unsigned long long *frame_photons, BatchState *state,
-                             HostMirror host, bool stamp, hipStream_t s);
+                             bool stamp, hipStream_t s);
 // Exclusive scan of frame hit counts: frame_offset[0..n_frames], total into state.
-hipError_t launch_frame_scan(const uint32_t *frame_hits, uint64_t n_frames,
+hipError_t launch_frame_scan(const uint32_t *frame_hits, const unsigned long long *frame_photons, uint64_t n_frames,
                              unsigned long long *frame_offset, BatchState *state, HostMirror host, hipStream_t s);
 // Copy each unit's staged hits to its place in the raster-order list.
 hipError_t launch_scatter(const uint32_t *unit_count, const uint64_t *unit_base,

@@ -675,8 +675,8 @@ pdc_status enqueue_tail(pdc_ctx *ctx, Batch &bt, bool main)
         HIP_TRY(ctx, launch_tail(a, s));
     } else {
         HIP_TRY(ctx, launch_frame_sums(b->unit_count, b->unit_photons, bt.n_frames, bt.upf, b->unit_local,
-                                       b->frame_hits, b->frame_photons, b->state, host, main, s));
-        HIP_TRY(ctx, launch_frame_scan(b->frame_hits, bt.n_frames, b->frame_offset, b->state, host, s));
+                                       b->frame_hits, b->frame_photons, b->state, main, s));
+        HIP_TRY(ctx, launch_frame_scan(b->frame_hits, b->frame_photons, bt.n_frames, b->frame_offset, b->state, host, s));
         if (bt.records)
             HIP_TRY(ctx, launch_scatter_records(b->unit_count, b->unit_base, b->unit_local, b->frame_offset, b->pool,
                                                 bt.n_units, bt.upf, ctx->dets[bt.det].p.photon_adu, bt.records,
