@@ -21,7 +21,7 @@
 // occupancy 0.01 it issues about 5,900 wave instructions per strip-frame of 30
 // own rows (the form before this one 8,000: 16 waves of four 16-lane groups,
 // values through LDS) and the VALUs are busy about 80 % of the time (66 %);
-// the batch takes 27.9 ms with default strips and frame groups, 42.6 ms before.
+// the kernel takes 23.8 ms, 38.1 ms before.
 // What the two changes behind that give:
 //   - few lanes a bank-row: a wave searches 8 (194-pixel banks) or 16 (96)
 //     medians at once, so the search's reductions, control and sort, as many

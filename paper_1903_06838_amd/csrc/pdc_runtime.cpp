@@ -452,18 +452,19 @@ bool plan_v2(pdc_ctx *ctx, Detector &d)
     d.seed_cap = 2 * d.hit_cap;
     d.v2_lds = frame_kernel_v2_lds_bytes(rmax, g.cols, g.bank_cols, nb, d.seed_cap, d.hit_cap);
     // the general kernel sized for one of these strips (own rows + halo), to
-    // redo the units whose seed lists overflow
+    // redo the units whose lists overflow: with the median as many rows a sort
+    // as the LDS holds; a mean sorts nothing, so room for one row is enough and
+    // two workgroups share a compute unit where they fit (640 CSPAD frames whose
+    // tile means leave a third of the pixels above threshold: 10.5 -> 8.1 ms)
     d.fb_ok = false;
-    {
-        const int sw = (int)next_pow2(g.bank_cols);
-        for (int srt = own_rows_max + 2; srt >= 1 && !d.fb_ok; --srt) {
-            const size_t lds = frame_kernel_v1_lds_bytes(own_rows_max, g.cols, nb, sw, srt, d.v2_max_unit_hits);
-            if (lds + 512 <= (size_t)ctx->max_lds) {
-                d.fb_ok = true;
-                d.fb_strip_rows = own_rows_max;
-                d.fb_sort_rows = srt;
-                d.fb_lds = lds;
-            }
+    for (int srt = d.p.cm_mode == PDC_CM_MEDIAN ? own_rows_max + 2 : 1; srt >= 1 && !d.fb_ok; --srt) {
+        const size_t lds = frame_kernel_v1_lds_bytes(own_rows_max, g.cols, nb, (int)next_pow2(g.bank_cols), srt,
+                                                     d.v2_max_unit_hits);
+        if (lds + 512 <= (size_t)ctx->max_lds) {
+            d.fb_ok = true;
+            d.fb_strip_rows = own_rows_max;
+            d.fb_sort_rows = srt;
+            d.fb_lds = lds;
         }
     }
     d.rank_width = d.p.sigma / (0.4f * (float)g.bank_cols);
