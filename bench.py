@@ -743,7 +743,7 @@ def main():
         # 5,920 rows make 198 strips of at most 30 own rows
         n_strips = -(-geom.n_tiles * geom.rows // 30)
         launches = args.steps + args.warmup
-        names = ["A", "bar_AB", "medians", "seeds", "local_max", "hit_writes", "bar_BA"]
+        names = ["A", "bar_1", "medians", "seeds", "bar_2", "local_max", "hit_writes"]
         rows = [[phase_buf[w * 8 + p] / (launches * N * n_strips) for p in range(7)] for w in range(16)]
         rows = [r for r in rows if any(r)]  # waves of a workgroup
         log("phase cycles per strip-frame per wave (s_memtime), %d launches of %d frames, %d strips:" % (
