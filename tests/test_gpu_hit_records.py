@@ -43,3 +43,32 @@ def test_record_frames(n):
         pdc.release_batch(c, b)
     finally:
         pdc.destroy(c)
+
+
+@pytest.mark.parametrize("cap", [1, 4095, 4096, 4097, 16384, 16385, 65536, 65537, 90000])
+def test_host_destinations(cap):
+    """Host destinations around the sizes of the pinned staging: the records of
+    one batch, whole and cut, against its device copy."""
+    import torch
+
+    from paper_1903_06838_amd import pdc
+
+    geom = synth.Geometry(2, 60, 388, 194)
+    ped, gain = synth.make_calibration(geom, 3)
+    raw = synth.make_frames(geom, ped, gain, 40, 0.06, 3)
+    c = pdc.create(0)
+    try:
+        det = pdc.calibrate(c, pdc.geometry(2, 60, 388, 194), ped, gain, pdc.params(3.0, 5.0, 3.0, 150.0, 0))
+        b = pdc.process_frames(c, det, torch.from_numpy(raw).cuda(), 40, raw.size // 8)
+        total = pdc.get_hits(c, b, 40, capacity=0)[1]
+        assert total > 65537
+        rec = torch.zeros((total, 4), dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        pdc.get_hits(c, b, 40, total, rec)
+        want = rec.cpu().numpy().tobytes()
+        for n in (cap, total, cap):
+            hits = pdc.get_hits(c, b, 40, capacity=n)[0]
+            assert hits.tobytes() == want[:16 * min(n, total)]
+        pdc.release_batch(c, b)
+    finally:
+        pdc.destroy(c)

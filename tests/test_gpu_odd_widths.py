@@ -109,3 +109,36 @@ def test_wide_banks_flood():
     got, path = _process(raw, ped, gain, 512, True)
     assert path in (2, 3)
     assert_same(got, want, corrected=True)
+
+
+@pytest.mark.parametrize("B,nb", [(97, 2), (199, 1), (300, 2), (512, 2)])
+def test_graph_and_kept_medians(B, nb):
+    """The same batches replayed from a graph, and their patches from kept
+    medians against those from kept Frames2."""
+    import torch
+
+    from paper_1903_06838_amd import pdc
+
+    geom, n = synth.Geometry(1, 40, B * nb, B), 4
+    ped, gain = synth.make_calibration(geom, 800 + B)
+    raw = synth.make_frames(geom, ped, gain, n, 0.03, 800 + B)
+    want = oracle_threads(raw, ped, gain, B)
+    dev = torch.from_numpy(raw).cuda()
+    ctx = pdc.create(0)
+    try:
+        got = []
+        for flag in (pdc.KEEP_CORRECTED, pdc.KEEP_MEDIANS):
+            det = pdc.calibrate(ctx, pdc.geometry(1, 40, B * nb, B), ped, gain, pdc.params(3.0, 5.0, 3.0, 150.0, flag))
+            graph = pdc.graph_create(ctx, det, dev, n, raw.size)
+            for _ in range(3):
+                b = pdc.graph_launch(ctx, graph)
+                hits, total, fh, fp, _ = pdc.get_hits(ctx, b, n)
+                assert_same(dict(hits=hits, total=total, frame_hits=fh, frame_photons=fp), want)
+                out = torch.zeros((total, 25), dtype=torch.float32, device="cuda")
+                torch.cuda.synchronize()
+                assert pdc.capture_patches(ctx, b, out, total) == total
+                pdc.release_batch(ctx, b)
+            got.append(out.cpu().numpy().view(np.uint32))
+        assert np.array_equal(got[0], got[1])
+    finally:
+        pdc.destroy(ctx)
