@@ -238,8 +238,9 @@ pdc_status pdc_process_frames_static(pdc_ctx *ctx, int32_t det, const uint16_t *
  * streams forked from hip_stream (NULL: the context's stream) and joined back
  * into it, so the detectors' kernels may overlap and work enqueued later on
  * hip_stream waits for all of them.  When there are 2 to 8 items and every
- * one takes the persistent kernel with the median common mode, keeping
- * neither Frames2 nor common-mode values, their frame kernels are one launch
+ * one takes the persistent kernel with banks of an even width up to 256 and
+ * the median common mode, keeping neither Frames2 nor common-mode values,
+ * their frame kernels are one launch
  * over the (detector, strip, frame group) work items of all of them, each
  * workgroup running the body compiled for its detector's lane layout and gain
  * mode (the Dark and Gain section's several darks and gains in one pass);

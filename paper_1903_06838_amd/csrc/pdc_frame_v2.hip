@@ -1281,7 +1281,7 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
 // Lane layouts (L lanes a bank-row, Q chunks of 8 columns and R single columns
 // a lane) by bank width.  Few lanes a bank-row pay the search's reductions,
 // control and sort once for more bank-rows (a wave holds 64 / L); the lane's
-// values, dark and 1/gain (3 V registers, with V = 4 Q + R) and the next
+// values, dark and 1/gain (3 V registers, with V = 8 Q + R) and the next
 // frame's words have to fit four waves per SIMD (128 registers).
 int v2_layout_of(int B)
 {
