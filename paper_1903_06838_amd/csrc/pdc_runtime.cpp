@@ -990,7 +990,8 @@ pdc_status detach_from_graph(pdc_ctx *ctx, Batch &bt)
     Buffers *b = take_buffers(ctx);
     if (!b) return fail(ctx, PDC_ENOMEM, "host allocation failed");
     const Detector &d = ctx->dets[bt.det];
-    pdc_status rc = ensure_buffers(ctx, b, bt.n_units, bt.n_frames, bt.pool_cap, corr_floats(d, bt), cm_floats(d, bt));
+    pdc_status rc = ensure_buffers(ctx, b, bt.n_units, bt.n_frames, bt.pool_cap, corr_floats(d, bt), cm_floats(d, bt),
+                                   meds_floats(d, bt));
     if (rc != PDC_OK) {
         ctx->spare.push_back(b);
         return rc;
