@@ -671,7 +671,7 @@ pdc_status enqueue_tail(pdc_ctx *ctx, Batch &bt, bool main)
         a.frame_offset = b->frame_offset;
         a.pool = b->pool;
         a.hits = b->hits;
-        a.hits_cap = b->cap_pool;
+        a.hits_cap = b->hits ? b->cap_pool : 0;  // (a caller that wants counts alone has no list)
         a.state = b->state;
         a.host = host;
         a.n_frames = (uint32_t)bt.n_frames;
@@ -687,7 +687,7 @@ pdc_status enqueue_tail(pdc_ctx *ctx, Batch &bt, bool main)
             HIP_TRY(ctx, launch_scatter_records(b->unit_count, b->unit_base, b->unit_local, b->frame_offset, b->pool,
                                                 bt.n_units, bt.upf, ctx->dets[bt.det].p.photon_adu, bt.records,
                                                 bt.records_cap, s));
-        else
+        else if (b->hits)
             HIP_TRY(ctx, launch_scatter(b->unit_count, b->unit_base, b->unit_local, b->frame_offset, b->pool,
                                         bt.n_units, bt.upf, b->hits, b->cap_pool, s));
     }
