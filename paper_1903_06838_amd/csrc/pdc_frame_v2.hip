@@ -952,7 +952,7 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
                     base = kNoBase;
                 } else if (total > 0) {
                     if (chunk_cur + total > chunk_end) {
-                        const uint64_t sz = total > kChunkHits ? (uint64_t)total : kChunkHits;
+                        const uint64_t sz = total > K->chunk_hits ? total : K->chunk_hits;
                         chunk_cur = atomicAdd(&K->state->cursor, (unsigned long long)sz);
                         chunk_end = chunk_cur + sz;
                     }

@@ -20,7 +20,8 @@ constexpr uint64_t kNoBase = ~0ull;
 constexpr int kV2Waves = PDC_V2_WAVES;
 constexpr int kV2Threads = kV2Waves * 64;
 constexpr int kV2GroupsPerCu = 16 / kV2Waves;
-// Staging chunk claimed by one workgroup from the batch-wide pool cursor.
+// Staging chunk claimed by one workgroup from the batch-wide pool cursor (the
+// persistent kernel's may be smaller where the pool's memory is bounded).
 constexpr uint64_t kChunkHits = 8192;
 
 // Device-side batch state, cleared by init_state before each run.
@@ -120,6 +121,7 @@ struct V2Args {
     uint32_t *invalid;
     float *meds;                  // as in FrameKernelArgs (median mode)
     int32_t hit_cap;              // hits per strip-frame held in LDS
+    uint32_t chunk_hits;          // staging chunk of a workgroup
     uint32_t row_mul, row_sh;     // at / W = (at * row_mul) >> row_sh for positions of a strip
     uint32_t bank_mul;            // col / B = (col * bank_mul) >> kBankShift for col < 2048
 };

@@ -130,6 +130,7 @@ struct Batch {
     bool capture = false;  // being captured into a graph: kernels only, no events or copies
     bool mix_one = false;  // its frame kernel ran in one launch with the other batches of a mixed call
     int fg_more = 1;       // frame groups x this beyond the detector's choice (one-launch mixed calls)
+    uint32_t chunk = kChunkHits;  // staging chunk of the persistent kernel's workgroups
     pdc_graph *graph = nullptr;  // launched from this graph, whose buffers it holds
     int gitem = 0;               // its item in that graph
     Buffers *buf = nullptr;
@@ -570,13 +571,12 @@ uint32_t v1_grid(uint64_t n_units)
     return (uint32_t)std::min<uint64_t>(n_units, 256 * 8);
 }
 
-uint64_t pool_capacity(const Detector &d, int path, uint64_t hit_capacity, uint32_t grid)
+uint64_t pool_capacity(const Detector &d, int path, uint64_t hit_capacity, uint32_t grid, uint64_t chunk = kChunkHits)
 {
     // Each workgroup may hold a partly used chunk, and each chunk may leave a
     // tail smaller than one unit's hits.
     uint64_t per_chunk_waste = path == 2 ? d.v2_max_unit_hits : d.max_unit_hits;
-    uint64_t slack = (uint64_t)grid * (kChunkHits + per_chunk_waste) +
-                     (hit_capacity / kChunkHits + 1) * per_chunk_waste;
+    uint64_t slack = (uint64_t)grid * (chunk + per_chunk_waste) + (hit_capacity / chunk + 1) * per_chunk_waste;
     return hit_capacity + slack;
 }
 
@@ -758,6 +758,7 @@ void fill_v2_args(const Detector &d, const Batch &bt, V2Args &a)
     a.sum_lo = d.sum_lo;
     a.sum_hi = d.sum_hi;
     a.hit_cap = d.hit_cap;
+    a.chunk_hits = bt.chunk;
     // n / W = (n * ceil(2^s / W)) >> s for n W <= 2^s, and n * ceil(2^s / W) <
     // 2^32 for the n <= 40960 positions that fit the LDS; likewise col / B
     const uint64_t positions = (uint64_t)d.rmax * a.W;
@@ -1377,34 +1378,56 @@ pdc_status pdc_process_frames_static(pdc_ctx *ctx, int32_t det, const uint16_t *
     b.pool = reinterpret_cast<uint2 *>(base + std::min(off, kStaticScratchBytes));
     b.cap_pool = pool_bytes / sizeof(uint2);
     bt.buf = &b;
-    // room for the staging chunks every workgroup may hold open
-    const uint64_t slack = pool_capacity(d, bt.path, 0, batch_grid(d, bt));
-    if (!fits || b.cap_pool <= slack)
-        return fail(ctx, PDC_EINVAL,
-                    "static: %llu frames need more than the %llu-byte static scratch (per-unit arrays and staging "
-                    "slack); process fewer frames per call",
-                    (unsigned long long)n_frames, (unsigned long long)kStaticScratchBytes);
-    bt.pool_cap = b.cap_pool;
+    // The pool has to hold the staging chunk that every workgroup may have open:
+    // the launch's own frame groups, or fewer, or (one group, still too many
+    // strips) smaller chunks.
+    auto room = [&](int path, int groups) {
+        set_path(d, bt, path);
+        bt.n_fg = std::min(bt.n_fg, groups);
+        bt.chunk = kChunkHits;
+        auto full = [&]() { return pool_capacity(d, path, 0, batch_grid(d, bt), bt.chunk) >= b.cap_pool; };
+        while (path == 2 && bt.n_fg > 1 && full()) --bt.n_fg;
+        while (path == 2 && bt.chunk > kChunkHits / 8 && full()) bt.chunk /= 2;
+        return !full();
+    };
     BatchState st{};
     auto wait_state = [&]() -> pdc_status {
         HIP_TRY(ctx, hipMemcpyAsync(&st, b.state, sizeof st, hipMemcpyDeviceToHost, bt.stream));
         HIP_TRY(ctx, hipStreamSynchronize(bt.stream));
         return PDC_OK;
     };
-    pdc_status rc = enqueue(ctx, bt);
-    if (rc == PDC_OK) rc = wait_state();
-    if (rc == PDC_OK && st.fallback && !st.overflow) {
-        if (bt.path == 2 && d.fb_ok) {
-            // strip-frames whose seeds overflowed the on-chip lists: the
-            // general kernel redoes them into the same staging pool
-            rc = enqueue_partial(ctx, bt, st.n_fallback);
-        } else {
-            set_path(d, bt, 1);
-            rc = enqueue(ctx, bt);
-        }
+    // A batch whose hits overflow the pool is run again with the fewest open
+    // chunks, then by the general kernel, whose units may be fewer.
+    const struct {
+        int path, groups;
+    } plans[] = {{2, INT32_MAX}, {2, 1}, {1, 1}};
+    int ran = 0;  // frame groups of the last run
+    for (const auto &plan : plans) {
+        if (plan.path == 2 && (!d.v2_ok || ran == plan.groups)) continue;
+        if (!fits || !room(plan.path, plan.groups)) continue;
+        ran = bt.n_fg;
+        bt.pool_cap = b.cap_pool;
+        pdc_status rc = enqueue(ctx, bt);
         if (rc == PDC_OK) rc = wait_state();
+        if (rc == PDC_OK && st.fallback && !st.overflow) {
+            if (bt.path == 2 && d.fb_ok) {
+                // strip-frames whose seeds overflowed the on-chip lists: the
+                // general kernel redoes them into the same staging pool
+                rc = enqueue_partial(ctx, bt, st.n_fallback);
+            } else {
+                set_path(d, bt, 1);
+                rc = enqueue(ctx, bt);
+            }
+            if (rc == PDC_OK) rc = wait_state();
+        }
+        if (rc != PDC_OK) return rc;
+        if (!st.overflow) break;
     }
-    if (rc != PDC_OK) return rc;
+    if (!ran)
+        return fail(ctx, PDC_EINVAL,
+                    "static: %llu frames need more than the %llu-byte static scratch (per-unit arrays and staging "
+                    "slack); process fewer frames per call",
+                    (unsigned long long)n_frames, (unsigned long long)kStaticScratchBytes);
     if (st.overflow)
         return fail(ctx, PDC_ENOMEM,
                     "static: the batch's hits overflow the staging pool of the static scratch (%llu entries); "
