@@ -553,9 +553,10 @@ typedef uint32_t u32_a2 __attribute__((aligned(2)));
 template <int L>
 constexpr int kV2Finish = L == 4 ? 4 : (L == 8 ? 3 : 2);
 
-// Bank-rows a lane group takes one after another in a frame: 256-column banks
-// need 16 lanes for four waves per SIMD (128 registers), and two passes keep
-// their strips as high as the others' (a strip loads two halo rows).
+// Bank-rows a lane group takes one after another in a frame (PP).  256-column
+// banks need 16 lanes for four waves per SIMD (128 registers), and two passes
+// keep their strips as high as the others' (a strip loads two halo rows).  So do
+// banks of 97 to 128 columns where a row holds many of them (v2_layout_of).
 // (Banks of 257 to 512 columns: 32 columns a lane, one pass, half the waves.)
 template <int L, int Q>
 constexpr int kV2Passes = L == 16 && Q == 2 ? 2 : 1;
@@ -575,10 +576,10 @@ __device__ __forceinline__ V2ArgsK fresh(V2ArgsK a)
 // One workgroup's work: work item `item` of the launch over A's strips and
 // frame groups (strip item % n_strips, frame group item / n_strips).  ODD: banks
 // of an odd width, whose last column has no partner.
-template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false, int P = kV2Passes<L, Q>>
 __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
 {
-    constexpr int V = 8 * Q + R, G = 64 / L, S = kV2Finish<L>, P = kV2Passes<L, Q>;
+    constexpr int V = 8 * Q + R, G = 64 / L, S = kV2Finish<L>;
     constexpr int kCntRegs = (kV2Threads / L * P + 63) / 64;  // bank-rows of a workgroup, 64 a register
     constexpr int kBitWords = (8 * L * Q + L * R + 31) / 32;  // of the widest bank of this layout
     static_assert(V <= 32, "a lane's values are bits of one mask");
@@ -1233,10 +1234,10 @@ __device__ __forceinline__ void frame_body(const V2ArgsK A, const int item)
 #undef PDC_PHASE
 }
 
-template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
+template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD, int P>
 __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2(V2Args)
 {
-    frame_body<L, Q, R, KEEP, CMM, MG, ODD>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
+    frame_body<L, Q, R, KEEP, CMM, MG, ODD, P>((V2ArgsK)__builtin_amdgcn_kernarg_segment_ptr(), block_item((int)blockIdx.x, (int)gridDim.x));
 }
 
 // Banks of 257 to 512 columns: 32 values a lane, with dark and 1/gain and the next
@@ -1252,7 +1253,11 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
 // of its own, so that items of unequal cost even out as they are handed
 // out), and each workgroup runs the body
 // compiled for its detector's lane layout and gain mode (median common mode,
-// Frames2 not kept: the variants v2_mix_variant lists).
+// Frames2 not kept: the variants v2_mix_variant lists).  TWO: with the bodies of
+// the two-pass layout of up to 128 columns, which mixes without it leave out (they
+// cost its other bodies registers: three mixed detectors' 1,000 frames 2.59 ms
+// with them, 2.53 without).
+template <bool TWO>
 __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu(4, 4))) frame_kernel_v2_mix(V2Mix)
 {
     const auto M = (const __attribute__((address_space(4))) V2Mix *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1274,6 +1279,12 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
     case 7: frame_body<8, 2, 0, false, 0, true>(A, it); break;
     case 8: frame_body<8, 3, 1, false, 0, true>(A, it); break;
     case 9: frame_body<16, 2, 0, false, 0, true>(A, it); break;
+    case 10:
+        if constexpr (TWO) frame_body<8, 2, 0, false, 0, false, false, 2>(A, it);
+        break;
+    case 11:
+        if constexpr (TWO) frame_body<8, 2, 0, false, 0, true, false, 2>(A, it);
+        break;
     default: break;
     }
 }
@@ -1283,59 +1294,69 @@ __global__ void __launch_bounds__(kV2Threads) __attribute__((amdgpu_waves_per_eu
 // control and sort once for more bank-rows (a wave holds 64 / L); the lane's
 // values, dark and 1/gain (3 V registers, with V = 8 Q + R) and the next
 // frame's words have to fit four waves per SIMD (128 registers).
-int v2_layout_of(int B)
+//
+// Layout 6 is layout 2 with two passes, for rows of more than 10 banks: one pass
+// holds 64 bank-rows, so less than four own rows a strip beside two halo rows.
+// 200 frames of 512 rows, one pass and two (us): 11 banks of 100 columns 428 and
+// 318, 13 banks 575 and 395, 18 banks 1,094 and 563; 12 banks of 128 columns 338
+// and 305.  With fewer banks a row the second pass costs more than the halo rows
+// it saves (8 tiles of 185 rows of 2 banks of 128: 109 and 127) or about as much
+// (8 of 128: 184 and 186), and two frames take longer (11 banks of 100: 20 and 25).
+int v2_layout_of(int B, int nb)
 {
-    return B <= 64 ? 0 : (B <= 96 ? 1 : (B <= 128 ? 2 : (B <= 200 ? 3 : (B <= 256 ? 4 : (B <= 512 ? 5 : -1)))));
+    if (B > 96 && B <= 128) return nb > 10 ? 6 : 2;
+    return B <= 64 ? 0 : (B <= 96 ? 1 : (B <= 200 ? 3 : (B <= 256 ? 4 : (B <= 512 ? 5 : -1))));
 }
 int v2_layout_bank_rows(int layout)
 {
-    return layout < 2 ? kV2Threads / 4
-                      : (layout < 4 ? kV2Threads / 8 : kV2Threads / 16 * (layout == 4 ? kV2Passes<16, 2> : 1));
+    constexpr int rows[] = {kV2Threads / 4, kV2Threads / 4, kV2Threads / 8, kV2Threads / 8,
+                            kV2Threads / 16 * kV2Passes<16, 2>, kV2Threads / 16, kV2Threads / 8 * 2};
+    return layout < 0 ? 0 : rows[layout];
 }
 
 size_t v2_layout_finish_bytes(int layout)
 {
-    return (size_t)kV2Threads * 4 * (layout < 2 ? kV2Finish<4> : (layout < 4 ? kV2Finish<8> : kV2Finish<16>));
+    return (size_t)kV2Threads * 4 * (layout < 2 ? kV2Finish<4> : (layout < 4 || layout == 6 ? kV2Finish<8> : kV2Finish<16>));
 }
 
-template <int L, int Q, int R, bool KEEP, int CMM, bool MG, bool ODD = false>
+template <int L, int Q, int R, int P, bool KEEP, int CMM, bool MG, bool ODD = false>
 static hipError_t launch_v2_k(const V2Args &a, uint32_t grid, size_t lds, hipStream_t s)
 {
-    auto k = frame_kernel_v2<L, Q, R, KEEP, CMM, MG, ODD>;
+    auto k = frame_kernel_v2<L, Q, R, KEEP, CMM, MG, ODD, P>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(grid), dim3(kV2Threads), lds, s, a);
     return hipGetLastError();
 }
 
-template <int L, int Q, int R>
+template <int L, int Q, int R, int P = kV2Passes<L, Q>>
 static hipError_t launch_v2_t(const V2Args &a, uint32_t grid, size_t lds, bool keep, hipStream_t s)
 {
     if (a.cm_mode < 0 || a.cm_mode > 2) return hipErrorInvalidValue;
     if (a.B & 1) {  // (the plan keeps the other odd-bank modes on the general kernel)
         if (a.cm_mode || a.gain_mode) return hipErrorInvalidValue;
-        return keep ? launch_v2_k<L, Q, R, true, 0, false, true>(a, grid, lds, s)
-                    : launch_v2_k<L, Q, R, false, 0, false, true>(a, grid, lds, s);
+        return keep ? launch_v2_k<L, Q, R, P, true, 0, false, true>(a, grid, lds, s)
+                    : launch_v2_k<L, Q, R, P, false, 0, false, true>(a, grid, lds, s);
     }
     switch (a.cm_mode * 4 + (keep ? 2 : 0) + (a.gain_mode ? 1 : 0)) {
-    case 0: return launch_v2_k<L, Q, R, false, 0, false>(a, grid, lds, s);
-    case 1: return launch_v2_k<L, Q, R, false, 0, true>(a, grid, lds, s);
-    case 2: return launch_v2_k<L, Q, R, true, 0, false>(a, grid, lds, s);
-    case 3: return launch_v2_k<L, Q, R, true, 0, true>(a, grid, lds, s);
-    case 4: return launch_v2_k<L, Q, R, false, 1, false>(a, grid, lds, s);
-    case 5: return launch_v2_k<L, Q, R, false, 1, true>(a, grid, lds, s);
-    case 6: return launch_v2_k<L, Q, R, true, 1, false>(a, grid, lds, s);
-    case 7: return launch_v2_k<L, Q, R, true, 1, true>(a, grid, lds, s);
-    case 8: return launch_v2_k<L, Q, R, false, 2, false>(a, grid, lds, s);
-    case 9: return launch_v2_k<L, Q, R, false, 2, true>(a, grid, lds, s);
-    case 10: return launch_v2_k<L, Q, R, true, 2, false>(a, grid, lds, s);
-    default: return launch_v2_k<L, Q, R, true, 2, true>(a, grid, lds, s);
+    case 0: return launch_v2_k<L, Q, R, P, false, 0, false>(a, grid, lds, s);
+    case 1: return launch_v2_k<L, Q, R, P, false, 0, true>(a, grid, lds, s);
+    case 2: return launch_v2_k<L, Q, R, P, true, 0, false>(a, grid, lds, s);
+    case 3: return launch_v2_k<L, Q, R, P, true, 0, true>(a, grid, lds, s);
+    case 4: return launch_v2_k<L, Q, R, P, false, 1, false>(a, grid, lds, s);
+    case 5: return launch_v2_k<L, Q, R, P, false, 1, true>(a, grid, lds, s);
+    case 6: return launch_v2_k<L, Q, R, P, true, 1, false>(a, grid, lds, s);
+    case 7: return launch_v2_k<L, Q, R, P, true, 1, true>(a, grid, lds, s);
+    case 8: return launch_v2_k<L, Q, R, P, false, 2, false>(a, grid, lds, s);
+    case 9: return launch_v2_k<L, Q, R, P, false, 2, true>(a, grid, lds, s);
+    case 10: return launch_v2_k<L, Q, R, P, true, 2, false>(a, grid, lds, s);
+    default: return launch_v2_k<L, Q, R, P, true, 2, true>(a, grid, lds, s);
     }
 }
 
 hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bool keep, hipStream_t s)
 {
-    const int lay = v2_layout_of(a.B);
+    const int lay = v2_layout_of(a.B, a.nb);
     if (a.B < 1 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return hipErrorInvalidValue;
     if (lay == 5) {
         if ((a.B & 1) || a.cm_mode || a.gain_mode) return hipErrorInvalidValue;
@@ -1350,35 +1371,41 @@ hipError_t launch_frame_kernel_v2(const V2Args &a, uint32_t grid, size_t lds, bo
     case 1: return launch_v2_t<4, 3, 0>(a, grid, lds, keep, s);
     case 2: return launch_v2_t<8, 2, 0>(a, grid, lds, keep, s);
     case 3: return launch_v2_t<8, 3, 1>(a, grid, lds, keep, s);
+    case 6: return launch_v2_t<8, 2, 0, 2>(a, grid, lds, keep, s);
     default: return launch_v2_t<16, 2, 0>(a, grid, lds, keep, s);
     }
 }
 
 int v2_mix_variant(const V2Args &a, bool keep)
 {
-    const int lay = v2_layout_of(a.B);
+    const int lay = v2_layout_of(a.B, a.nb);
     if (keep || a.cm_mode || a.meds || a.B < 1 || (a.B & 1) || lay == 5 || lay < 0 || a.rmax * a.nb > v2_layout_bank_rows(lay)) return -1;
+    if (lay == 6) return a.gain_mode ? 11 : 10;
     return lay + (a.gain_mode ? 5 : 0);
 }
 
 size_t frame_kernel_v2_mix_static_lds()
 {
+    // (TWO's bodies are the other's and two more)
     hipFuncAttributes fa{};
-    if (hipFuncGetAttributes(&fa, (const void *)frame_kernel_v2_mix) != hipSuccess) return SIZE_MAX;
+    if (hipFuncGetAttributes(&fa, (const void *)frame_kernel_v2_mix<true>) != hipSuccess) return SIZE_MAX;
     return fa.sharedSizeBytes;
 }
 
 hipError_t launch_frame_kernel_v2_mix(const V2Mix &m, size_t lds, hipStream_t s)
 {
     if (m.n < 1 || m.n > kMixMax) return hipErrorInvalidValue;
-    for (int d = 0; d < m.n; ++d)
+    bool two = false;
+    for (int d = 0; d < m.n; ++d) {
         if (m.variant[d] < 0 || m.first[d + 1] < m.first[d]) return hipErrorInvalidValue;
+        two |= m.variant[d] >= 10;
+    }
     const uint32_t grid = (uint32_t)m.first[m.n];
     if (grid == 0) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute((const void *)frame_kernel_v2_mix, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds);
+    const auto k = two ? frame_kernel_v2_mix<true> : frame_kernel_v2_mix<false>;
+    hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(frame_kernel_v2_mix, dim3(grid), dim3(kV2Threads), lds, s, m);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(kV2Threads), lds, s, m);
     return hipGetLastError();
 }
 

@@ -127,10 +127,10 @@ struct V2Args {
 };
 
 constexpr int kBankShift = 20;
-// Compiled lane layout for banks of B pixels (-1: none), the bank-rows a
+// Compiled lane layout for banks of B pixels, nb a row (-1: none), the bank-rows a
 // workgroup holds with it and the bytes of its medians' finish scratch, which
 // lies in a hit list.
-int v2_layout_of(int B);
+int v2_layout_of(int B, int nb);
 // Workgroups a compute unit holds at once.
 inline int v2_groups_per_cu(int B) { return B > 256 ? 1 : kV2GroupsPerCu; }
 int v2_layout_bank_rows(int layout);

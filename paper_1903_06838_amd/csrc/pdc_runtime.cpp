@@ -382,7 +382,7 @@ bool plan_v2(pdc_ctx *ctx, Detector &d)
     if (((g.bank_cols & 1) || g.bank_cols > 256) && (g.gain_mode || d.p.cm_mode != PDC_CM_MEDIAN)) return false;
     if ((g.bank_cols & 1) && g.bank_cols > 256) return false;
     const int nb = g.cols / g.bank_cols;
-    const int layout = v2_layout_of(g.bank_cols);
+    const int layout = v2_layout_of(g.bank_cols, nb);
     const int max_bank_rows = v2_layout_bank_rows(layout);
     int rmax_lim = max_bank_rows / nb;
     // room in LDS for seeds on a twelfth of the strip's pixels at least (1024-
