@@ -75,6 +75,7 @@ struct Detector {
 };
 
 constexpr uint64_t kFmtChunk = 16384, kFmtSlots = 4;  // records of a chunk, chunks in flight to the host
+constexpr uint64_t kFmtCopy = 1 << 15;     // records from which page-locked memory is left to the copy engine
 constexpr uint64_t kMirrorFrames = 65536;  // frames whose counts the kernels also write to pinned memory
 constexpr uint64_t kMirrorInline = 4096;   // of them, and hit records, in the allocation of the state
 
@@ -184,6 +185,8 @@ struct pdc_ctx {
     std::string err;
     HitRecord *fmt_buf = nullptr;  // pinned staging of host-destination get_hits: kFmtSlots chunks
     hipEvent_t fmt_done[kFmtSlots] = {};
+    HitRecord *fmt_dev = nullptr;  // device staging of get_hits to page-locked memory
+    uint64_t fmt_dev_cap = 0;
     bool force_v1 = false;         // PDC_FORCE_GENERAL=1 in the environment
     int strip_rows = 0;            // PDC_STRIP_ROWS=n: own rows per strip at most n for new detectors
     bool tight_pool = false;       // PDC_DEBUG_TIGHT_POOL=1: first staging holds hit_capacity only
@@ -1100,6 +1103,15 @@ pdc_status setup_batch(pdc_ctx *ctx, int32_t det, const uint16_t *frames_dev, ui
     return PDC_OK;
 }
 
+// Memory that the copy engine reaches: page-locked, or not the host's own.
+bool page_locked(const void *p)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+    (void)hipGetLastError();  // unknown to the runtime: ordinary memory
+    return false;
+}
+
 // An enqueued batch becomes outstanding under the next id.
 uint64_t register_batch(pdc_ctx *ctx, Batch &bt)
 {
@@ -1207,6 +1219,7 @@ pdc_status pdc_destroy(pdc_ctx *ctx)
             hipFree(d.d_strips);
         }
     if (ctx->fmt_buf) hipHostFree(ctx->fmt_buf);
+    hipFree(ctx->fmt_dev);
     for (hipEvent_t e : ctx->fmt_done)
         if (e) hipEventDestroy(e);
     hipStreamDestroy(ctx->stream);
@@ -1543,11 +1556,25 @@ pdc_status pdc_get_hits(pdc_ctx *ctx, uint64_t batch, pdc_hit *dst, uint64_t dst
             HIP_TRY(ctx, launch_format_hits(b->hits, b->frame_offset, bt->n_frames, 0, n_out, E, b->host_records, cs));
             HIP_TRY(ctx, hipStreamSynchronize(cs));
             std::memcpy(dst, b->host_records, n_out * sizeof(pdc_hit));
+        } else if (n_out >= kFmtCopy && page_locked(dst)) {
+            // the copy engine fills page-locked memory at the link's rate, a host
+            // thread's copies out of the staging below do not (us, by it and by the
+            // staging: 16,384 records 27 and 23, 32,768 32 and 33, 262,144 98 and 171,
+            // 35 million 10,100 and 28,000 to 31,000)
+            const uint64_t chunk = std::min((uint64_t)1 << 24, n_out);
+            HIP_TRY(ctx, grow(&ctx->fmt_dev, ctx->fmt_dev_cap, chunk));
+            for (uint64_t first = 0; first < n_out; first += chunk) {
+                const uint64_t n = std::min(chunk, n_out - first);
+                HIP_TRY(ctx, launch_format_hits(b->hits, b->frame_offset, bt->n_frames, first, n, E, ctx->fmt_dev, cs));
+                HIP_TRY(ctx, hipMemcpyAsync(dst + first, ctx->fmt_dev, n * sizeof(pdc_hit), hipMemcpyDeviceToHost, cs));
+            }
+            HIP_TRY(ctx, hipStreamSynchronize(cs));
         } else {
             // the kernel writes the records straight to pinned memory, a chunk
             // per slot, while the host copies the slots before it out (16 CSPAD
-            // frames' 370,000 records through a device buffer and pageable
-            // copies: 439 us the call, 325 us so)
+            // frames' 354,000 records through a device buffer and pageable
+            // copies: 352 us, 230 us so; 35 million 32,600 and 32,600, to memory
+            // that was never touched 54,000 and 43,000)
             constexpr uint64_t chunk = kFmtChunk, slots = kFmtSlots;
             if (!ctx->fmt_buf)
                 HIP_TRY(ctx, hipHostMalloc((void **)&ctx->fmt_buf, chunk * slots * sizeof(HitRecord), hipHostMallocCoherent));
