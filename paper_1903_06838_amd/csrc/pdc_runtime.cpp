@@ -274,8 +274,9 @@ pdc_status check_params(const pdc_params *p, float *t_seed, float *t_nb)
         if (!(std::isfinite(p->n_cm) && p->n_cm >= 0.0f && std::isfinite(tc)))
             return fail(nullptr, PDC_EINVAL, "n_cm must be finite and >= 0 with n_cm*sigma finite");
     }
-    if (t_seed) *t_seed = ts;
-    if (t_nb) *t_nb = tn;
+    // (-0, of n_seed = -0, becomes +0: the frame kernel tests the sign of fl(t - v))
+    if (t_seed) *t_seed = ts + 0.0f;
+    if (t_nb) *t_nb = tn + 0.0f;
     return PDC_OK;
 }
 
