@@ -663,25 +663,24 @@ __device__ __forceinline__ uint64_t wave_frame_of(const unsigned long long *fram
 }
 
 // Hits first .. first + n - 1 as 16-byte records.  24 bytes a hit bound it, so
-// a wave takes 64 kFormatRows consecutive hits, finds the frames of its first
-// and last one once, and has a lane search between them only where they differ
-// (a search over all frames per hit, one hit a thread, moved 1.65 TB/s: 10,000
-// CSPAD frames' 220 million hits 3.21 ms, now 0.98 ms, 5.4 TB/s).
-constexpr int kFormatRows = 8;
-
+// a wave takes 64 R consecutive hits, finds the frames of its first and last one
+// once, and has a lane search between them only where they differ (a search over
+// all frames per hit, one hit a thread, moved 1.65 TB/s: 10,000 CSPAD frames' 220
+// million hits 3.21 ms, now 0.98 ms, 5.4 TB/s).
+template <int R>
 __global__ void __launch_bounds__(256)
 format_hits_kernel(const uint2 *hits, const unsigned long long *frame_offset, uint64_t n_frames,
                    uint64_t first, uint64_t n, float photon_adu, HitRecord *out)
 {
-    constexpr uint64_t per_wave = 64 * kFormatRows;
+    constexpr uint64_t per_wave = 64 * R;
     const int lane = threadIdx.x & 63;
     const uint64_t wave = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint64_t i0 = wave * per_wave;
     if (i0 >= n) return;
     const uint64_t last = (n - i0 < per_wave ? n : i0 + per_wave) - 1;
-    uint2 h[kFormatRows];
+    uint2 h[R];
 #pragma unroll
-    for (int r = 0; r < kFormatRows; ++r) {
+    for (int r = 0; r < R; ++r) {
         const uint64_t i = i0 + 64u * r + lane;
         h[r] = hits[first + (i <= last ? i : last)];
     }
@@ -691,7 +690,7 @@ format_hits_kernel(const uint2 *hits, const unsigned long long *frame_offset, ui
                             ? f0
                             : wave_frame_of(frame_offset, f0 + 1, n_frames, first + last, lane);
 #pragma unroll
-    for (int r = 0; r < kFormatRows; ++r) {
+    for (int r = 0; r < R; ++r) {
         const uint64_t i = i0 + 64u * r + lane;
         if (i > last) return;
         uint64_t lo = f0, hi = f1 + 1;
@@ -710,14 +709,21 @@ format_hits_kernel(const uint2 *hits, const unsigned long long *frame_offset, ui
     }
 }
 
+// One row a wave for short lists: their time is one wave's chain of searches,
+// which the rows repeat (the call with a device destination, rows 1, 2 and 8, us:
+// 968 hits of 100 small frames 14.0, 14.6, 19.5, by a search per hit 13.7; 100,000
+// of 10 ePix100 frames 13.8, 14.0, 15.6, 13.9).  Long lists take two, which share
+// the search: 300,000 hits of 64 CSPAD frames 14.5, 14.4, 15.9; 11 million 55.9,
+// 50.9, 52.4, by a search per hit 88.8.
 hipError_t launch_format_hits(const uint2 *hits, const unsigned long long *frame_offset,
                               uint64_t n_frames, uint64_t first, uint64_t n, float photon_adu,
                               HitRecord *out, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    uint64_t blocks = (n + 256 * kFormatRows - 1) / (256 * kFormatRows);
-    hipLaunchKernelGGL(format_hits_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, hits,
-                       frame_offset, n_frames, first, n, photon_adu, out);
+    const int rows = n < (1u << 19) ? 1 : 2;
+    const uint64_t blocks = (n + 256 * rows - 1) / (256 * rows);
+    hipLaunchKernelGGL(rows == 1 ? format_hits_kernel<1> : format_hits_kernel<2>, dim3((uint32_t)blocks), dim3(256), 0,
+                       s, hits, frame_offset, n_frames, first, n, photon_adu, out);
     return hipGetLastError();
 }
 

@@ -76,3 +76,37 @@ def test_more_than_the_staging():
         assert torch.equal(dst.cuda(), dev)
     finally:
         pdc.destroy(ctx)
+
+
+def test_long_lists():
+    """Records of frames that are empty, hold one hit or many, in lists around
+    the length from which a wave takes two rows of hits."""
+    import torch
+
+    from paper_1903_06838_amd import pdc
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    n, rows = 30000, 1 << 19
+    geom = synth.Geometry(1, 16, 64, 32)
+    kind = np.random.default_rng(6).integers(0, 3, n)
+    raw = np.full((n, *geom.shape), 1000, np.uint16)
+    raw[kind == 1, 0, 8, 31] = 1160
+    raw[kind == 2, :, 1::3, 1::5] = 1160
+    ctx = pdc.create(0)
+    try:
+        ped, gain = np.full(geom.shape, 1000.0, np.float32), np.ones(geom.shape, np.float32)
+        det = pdc.calibrate(ctx, pdc.geometry(*geom.shape, 32), ped, gain, pdc.params())
+        b = pdc.process_frames(ctx, det, torch.from_numpy(raw.view(np.int16)).cuda(), n, raw.size // 8)
+        total = pdc.get_hits(ctx, b, n, capacity=0)[1]
+        frame = torch.from_numpy(np.repeat(np.arange(n), np.array([0, 1, 65])[kind]).astype(np.int32)).cuda()
+        one, many = [8 * 64 + 31], [64 * r + c for r in range(1, 16, 3) for c in range(1, 64, 5)]
+        pixel = torch.tensor(np.concatenate([([], one, many)[k] for k in kind]).astype(np.int32)).cuda()
+        assert total == len(frame) == len(pixel) > rows + 200
+        for cap in (rows - 1, rows, rows + 1, rows + 63, rows + 64, rows + 65, rows + 127, rows + 128, rows + 129, total):
+            rec = torch.full((cap + 2, 4), -1, dtype=torch.int32, device="cuda")
+            torch.cuda.synchronize()
+            pdc.get_hits(ctx, b, n, capacity=cap, dst_dev=rec)
+            assert torch.equal(rec[:cap, 0], frame[:cap]) and torch.equal(rec[:cap, 1], pixel[:cap])
+            assert bool((rec[:cap, 3] == 1).all()) and bool((rec[cap:] == -1).all())
+    finally:
+        pdc.destroy(ctx)
