@@ -1936,7 +1936,15 @@ pdc_status capture(pdc_ctx *ctx, uint64_t batch, float *patches, uint16_t *input
     c.unit_count = b->unit_count;
     c.unit_local = b->unit_local;
     c.frame_offset = b->frame_offset;
-    c.n_frames = bt->n_frames;
+    c.n_frames = c.batch_frames = bt->n_frames;
+    c.batch_hits = b->host_state->total;
+    if (n < b->host_state->total && bt->n_frames <= kMirrorFrames) {
+        // the destination holds the first frames' hits only (10,000 patches of 64
+        // CSPAD frames' 2.7 million, from kept medians 18 us, with waves for all
+        // frames 43; from Frames2 16 and 30)
+        uint64_t hits = 0;
+        for (c.n_frames = 0; hits < n; ++c.n_frames) hits += b->host_hits[c.n_frames];
+    }
     c.upf = (uint32_t)bt->upf;
     c.n = n;
     c.patches = patches;

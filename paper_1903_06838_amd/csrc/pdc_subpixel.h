@@ -72,7 +72,8 @@ struct CaptureArgs {
     const uint2 *hits;
     const uint32_t *unit_count, *unit_local;   // [n_frames][upf]
     const unsigned long long *frame_offset;    // [n_frames + 1]
-    uint64_t n_frames;
+    uint64_t n_frames;                         // frames that hold the first n hits
+    uint64_t batch_frames, batch_hits;         // of the whole batch
     uint32_t upf;
     uint64_t frames_per_item;                  // set by the launch
     uint32_t parts;                            // waves that share a unit's run (set by the launch)

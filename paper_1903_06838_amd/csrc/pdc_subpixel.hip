@@ -1139,7 +1139,8 @@ __global__ void __launch_bounds__(64 * kPatchWaves) capture_kernel(CaptureArgs a
 // 114, 32: 100 at the size above), and where there are more a strip's frames
 // taken one after another.  Batches of fewer units share each unit's run among
 // up to 16 waves (3 Jungfrau frames at occupancy 0.024, about 500 hits a
-// strip: 16 us; by a wave a unit, and a load a pixel for gain ranges, 158).
+// strip: 16 us; by a wave a unit, and a load a pixel for gain ranges, 158), no
+// more than four times as many as the batch's mean run fills with 12 hits each.
 hipError_t launch_capture(CaptureArgs a, uint32_t n_cu, hipStream_t s)
 {
     if (a.n == 0 || a.n_frames == 0 || a.upf == 0) return hipSuccess;
@@ -1147,7 +1148,8 @@ hipError_t launch_capture(CaptureArgs a, uint32_t n_cu, hipStream_t s)
     a.frames_per_item = units / want > 1 ? units / want : 1;
     if (a.frames_per_item > a.n_frames) a.frames_per_item = a.n_frames;
     const uint64_t items = (a.n_frames + a.frames_per_item - 1) / a.frames_per_item * a.upf;
-    const uint64_t parts = (want + units - 1) / units;
+    const uint64_t all = a.batch_frames * (uint64_t)a.upf * kPatchHits, fill = (4 * a.batch_hits + all - 1) / all;
+    const uint64_t parts = (want + units - 1) / units < fill ? (want + units - 1) / units : fill;
     a.parts = (uint32_t)(parts < 1 ? 1 : (parts > 16 ? 16 : parts));
     const uint64_t blocks = (items * a.parts + kPatchWaves - 1) / kPatchWaves;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
