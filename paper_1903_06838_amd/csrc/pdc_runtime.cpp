@@ -915,15 +915,19 @@ pdc_status enqueue_partial(pdc_ctx *ctx, Batch &bt, uint64_t n_list)
     return enqueue_tail(ctx, bt, false);
 }
 
-// Frame groups of a persistent launch: each workgroup takes one strip for a
-// contiguous range of frames, one workgroup per compute unit at a time, and
-// spends an extra pipeline iteration draining.  The count minimises
-// rounds x (frames per group + 1), the iterations a compute unit runs: large
-// batches get enough groups to fill whole rounds of the chip (CSPAD's 198
-// strips alone would leave 58 of 256 units idle), small ones stay in one round.
+// Frame groups of a persistent launch over n_cu workgroups at a time (two share a
+// compute unit): each workgroup takes one strip for a contiguous range of frames
+// and spends an extra pipeline iteration draining.  The count minimises rounds x
+// (frames per group + 1), the iterations a place on the chip runs: large batches
+// get enough groups to fill whole rounds of the chip (CSPAD's 198 strips alone
+// would leave 314 of 512 places empty), small ones stay in one round.
 int frame_groups(int n_cu, int n_strips, uint64_t n_frames, int mult)
 {
-    const int max_fg = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, n_frames));
+    // At most 64 groups where their workgroups fill the chip, up to 128 of a
+    // detector of few strips, whose workgroups 64 leave it half idle (20,000 frames
+    // of 16 x 32 pixels, one strip: 1,352 and 742 us).
+    const uint64_t most = std::max(64, std::min(128, n_cu / std::max(1, n_strips)));
+    const int max_fg = (int)std::max<uint64_t>(1, std::min(most, n_frames));
     int best = 1;
     uint64_t best_cost = ~0ull;
     for (int g = 1; g <= max_fg; ++g) {
