@@ -215,7 +215,8 @@ pdc_status pdc_process_frames(pdc_ctx *ctx, int32_t det, const uint16_t *frames_
  * frames_dev: DEVICE uint16 [n_frames][n_tiles][rows][cols] as for
  *   pdc_process_frames.
  * hits_dev: DEVICE records, room for hits_capacity (the first
- *   min(total, hits_capacity) hits in (frame, pixel) order are written).
+ *   min(total, hits_capacity) hits in (frame, pixel) order are written); may be
+ *   NULL with hits_capacity = 0.
  * frame_hits_dev (uint32 [n_frames]) and frame_photons_dev (uint64
  *   [n_frames]): DEVICE per-frame counts and photon totals.
  * *n_hits_total (may be NULL): the true total.
@@ -361,8 +362,8 @@ pdc_status pdc_stream_read(pdc_ctx *ctx, const void *src_dev, uint64_t bytes, vo
  * per graph at a time: ESTATE until the previous one is released.  A batch that
  * needs recomputing from the start (staging overflow beyond hit_capacity, or
  * no general-kernel plan for overflowing seed lists) is moved to buffers of its
- * own, so results stay exact and the graph stays valid.  Batch timing reports
- * the whole graph as main_ms.
+ * own, so results stay exact and the graph stays valid.  pdc_batch_timing of a
+ * graph's batch: main_ms is its frame kernel, total_ms the whole graph.
  * pdc_graph_destroy frees the graph; ESTATE while its batch is outstanding.
  * pdc_destroy frees graphs still alive.  A graph is used from its context's
  * thread, as the context is. */

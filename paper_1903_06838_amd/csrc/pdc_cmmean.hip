@@ -6,8 +6,9 @@
 //   v <- v - CM_s  (the next stage segments the corrected values).
 // S is the exact sum of the noise values rounded once to binary32 (ties to
 // even), so no order of summation enters: each lane adds its values into
-// binary64 limbs exactly, and the lanes' limbs are put together in a
-// multiword integer (pdc_exact.h).
+// binary64 limbs exactly, and the totals of two limbs are rounded from their
+// binary64 sum and its error, of more put together in a multiword integer
+// (pdc_exact.h).
 // The frame kernels then subtract CM_1, CM_2, CM_3 in turn (zeros for unused
 // stages: x - 0 = x bit for bit).
 #include <hip/hip_runtime.h>

@@ -19,7 +19,8 @@
 // 24 significant bits).  Limb i of a lane (or of a group of lanes) adds its
 // q_i: with at most 2^(53 - K) values per accumulator every partial sum is an
 // integer below 2^53, so the binary64 additions are exact in any order.  The
-// limb totals are then put together in a multiword integer and rounded once.
+// limb totals are then rounded once: two from their binary64 sum and its error
+// (limbs2_round), more put together in a multiword integer.
 //
 // Groups.  Eight values whose window spans at most 50 bits have an exact binary64
 // sum, so they are added first and split into limbs once: a conversion, 7/8 of

@@ -18,10 +18,10 @@
 //     left of it in its bank-row (bitmap popcount).
 //
 // What bounds it: VALU instructions.  On the 10,000-frame CSPAD batch at
-// occupancy 0.01 it issues about 5,900 wave instructions per strip-frame of 30
+// occupancy 0.01 it issues about 6,100 wave instructions per strip-frame of 30
 // own rows (the form before this one 8,000: 16 waves of four 16-lane groups,
 // values through LDS) and the VALUs are busy about 80 % of the time (66 %);
-// the kernel takes 23.8 ms, 38.1 ms before.
+// the kernel takes 23.7 ms, 38.1 ms before.
 // What the two changes behind that give:
 //   - few lanes a bank-row: a wave searches 8 (194-pixel banks) or 16 (96)
 //     medians at once, so the search's reductions, control and sort, as many
@@ -313,7 +313,7 @@ __device__ __forceinline__ int slot_off(int v, int gl)
 }
 
 // Exact element of rank k (0-based, ascending) among the nval finite values
-// held by an L-lane group (V = 4 Q + R values per lane, absent values +inf,
+// held by an L-lane group (V = 8 Q + R values per lane, absent values +inf,
 // slot v also at src[slot_off(v)] in LDS); every group of the wave searches
 // its own bank at once.  Bracketing search on counts, count(x < lo) <= k <
 // count(x < hi) throughout, with the lane masks of both bounds kept: the first
@@ -329,11 +329,13 @@ __device__ __forceinline__ int slot_off(int v, int gl)
 //
 // S and the margin of the second bound.  The work of a step is paid by the
 // whole wave while any of its 64 / L groups needs it, so the bracket that is
-// left to the sort is wide enough that few groups miss it or overfill it.  A
-// model of this search on CSPAD-like banks (194 values, 8 lanes a bank) takes
-// an extra count in 66 % of the waves with 16 values left to the sort, and in
-// 19 % with 32 and a margin of 8 to 9 ranks; with 96-pixel banks on 4 lanes
-// 60 % with 16 (32 would cost 8 registers a lane in the sort).
+// left to the sort is wide enough that few groups miss it or overfill it.  Counts
+// beyond the first two, a wave, in a model of this search at occupancy 0.01:
+// CSPAD's 194 columns on 8 lanes 0.83 with 16 values left to the sort, 0.29 with
+// 24 and a margin of 6 ranks (4: 0.37, 7: 0.33), 0.14 with 32 and 7 (a longer
+// sort for every wave; margins of 5 to 10 measured within 0.5 %); 96 columns on 4
+// lanes 0.73 with 16 and 4 (3: 0.76, 5: 0.80), where more values would cost
+// registers in the sort; 256 columns on 16 lanes 0.09 with 32 and 7.
 template <int L, int Q, int R, int S, bool SPARSE>
 __device__ __forceinline__ float group_median(const float (&x)[8 * Q + R], const float *src, int nval, int k, float rw,
                                               bool act, float *gsc, bool full, const SortSides<L> &sd)
@@ -484,7 +486,7 @@ struct V2Layout {
 // (charge and strip position of each local maximum), bitmaps and counts are
 // double-buffered by frame parity, the seed counts kept for four frames (frame
 // mod 4).  Seeds and hits name their pixel by its position in the strip's
-// loaded rows (16 bits).  The median finish scratch (16 KiB) lies in the
+// loaded rows (16 bits).  The median finish scratch (4 to 8 KiB) lies in the
 // hit list of the frame's own parity, which is not in use then.
 __device__ __host__ __forceinline__ V2Layout v2_layout(int rmax, int W, int B, int nb, int seed_cap, int hit_cap)
 {

@@ -507,9 +507,9 @@ hipError_t launch_scatter(const uint32_t *unit_count, const uint64_t *unit_base,
 // totals of the frames that start in its units, and copies its runs.  The last
 // workgroup publishes the batch's state.  Launches and the gaps between them
 // bound such batches: 16 CSPAD frames (3,168 units) took 13 us in the three
-// kernels and 10 us more for a copy of the state, 7 us here.  The sums over the
+// kernels and 10 us more for a copy of the state, 6 us here.  The sums over the
 // units before grow with their number: at 64 CSPAD frames (12,672 units) it is
-// 11 us against 14, and larger batches keep the three kernels.
+// 10 us against 14, and larger batches keep the three kernels.
 constexpr uint32_t kTailUnits = 16384, kTailUpf = 1024;
 
 bool tail_fits(uint64_t n_units, int32_t upf)
@@ -666,7 +666,7 @@ __device__ __forceinline__ uint64_t wave_frame_of(const unsigned long long *fram
 // a wave takes 64 R consecutive hits, finds the frames of its first and last one
 // once, and has a lane search between them only where they differ (a search over
 // all frames per hit, one hit a thread, moved 1.65 TB/s: 10,000 CSPAD frames' 220
-// million hits 3.21 ms, now 0.98 ms, 5.4 TB/s).
+// million hits 3.21 ms, now 0.96 ms, 5.5 TB/s).
 template <int R>
 __global__ void __launch_bounds__(256)
 format_hits_kernel(const uint2 *hits, const unsigned long long *frame_offset, uint64_t n_frames,

@@ -446,9 +446,9 @@ bool plan_v2(pdc_ctx *ctx, Detector &d)
     // of each tile part (two parts when the strip crosses a tile edge)
     d.v2_max_unit_hits = (uint32_t)((own_rows_max + 3) / 2) * (uint32_t)((g.cols + 1) / 2);
     // seed list (2 bytes an entry) and two hit lists half as long (6 bytes):
-    // as large as the workgroup's LDS allows (the kernel's registers admit one
-    // workgroup per compute unit anyway), a hit list at least the medians'
-    // finish scratch; 512 bytes stay free for the kernel's static LDS (the
+    // as large as the workgroup's share of the LDS allows (the kernel's registers
+    // admit no more workgroups), a hit list at least the medians' finish scratch;
+    // 512 bytes stay free for the kernel's static LDS (the
     // one-launch mixed kernel holds every body's own variables)
     const size_t base = lds_base(rmax);
     if (base + 16 * min_hits > lds_cap) return false;
